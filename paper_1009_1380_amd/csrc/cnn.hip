@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <new>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "../../include/radon.h"
@@ -39,14 +40,34 @@ radon_status_t errf(radon_status_t st, const char* fmt, ...) {
     return rn::api_fail(st, buf);
 }
 
-int pad8(int k) { return (k + 7) / 8 * 8; }
+int pad_to(int k, int m) { return (k + m - 1) / m * m; }
+
+// A bf16 operand layout of a layer's weights (cnn_kernels.hpp, WL_*).
+struct Packed {
+    uint16_t* p = nullptr;
+    int layout = cnn::WL_CHUNK, rows = 0;   // rows: output channels padded to 32 (WL_CHUNK)
+    size_t count = 0;                       // bf16 values
+};
+
+// The layout that the convolution of `cin` into `cout` channels reads.
+Packed packed_for(int cin, int cout) {
+    Packed q;
+    if (cin == 1 && cout == 32) {
+        q.layout = cnn::WL_C1;
+        q.count = 2 * 32 * 8;
+    } else {
+        q.rows = pad_to(cout, 32);
+        q.count = (size_t)pad_to(cin, 16) / 16 * 18 * q.rows * 8;
+    }
+    return q;
+}
 
 struct Conv {
-    int cin = 0, cout = 0, Kp = 0, Kpt = 0;
+    int cin = 0, cout = 0;
     float *w = nullptr, *b = nullptr;          // parameters (float32)
     float *gw = nullptr, *gb = nullptr;        // gradients
     float *mw = nullptr, *vw = nullptr, *mb = nullptr, *vb = nullptr;   // Adam moments
-    uint16_t *Wg = nullptr, *Wt = nullptr;     // bf16 GEMM layouts (forward, data gradient)
+    Packed fwd, dgr;                           // bf16 operands (forward, data gradient)
     size_t nw() const { return (size_t)cout * cin * 9; }
 };
 
@@ -59,28 +80,35 @@ struct radon_cnn_s {
     int B = 0, H = 0, W = 0;
     int step = 0;
     Conv conv[NCONV];
-    std::vector<void*> allocs;
-    // activations (bf16) and gradients
-    uint16_t *x16 = nullptr, *e0 = nullptr, *p0 = nullptr, *e1 = nullptr, *p1 = nullptr, *e2 = nullptr,
-             *p2 = nullptr, *e3 = nullptr, *u3 = nullptr, *re = nullptr, *d2 = nullptr, *u2 = nullptr,
-             *rf = nullptr, *d1 = nullptr, *u1 = nullptr, *rg = nullptr, *d0 = nullptr;
-    uint16_t *gy = nullptr, *ga = nullptr, *gb = nullptr, *gc = nullptr;   // scratch gradients (largest size)
-    float *part = nullptr, *loss_part = nullptr;
-    size_t part_n = 0;
+    void* arena = nullptr;                               // all device memory
+    std::vector<std::pair<void**, size_t>> wanted;       // what it will hold: pointer, offset
+    size_t bytes = 0;
+    // activations (bf16 planes), the ReLU masks of layers 0..6, gradients
+    uint16_t *e0 = nullptr, *p0 = nullptr, *e1 = nullptr, *p1 = nullptr, *e2 = nullptr, *p2 = nullptr,
+             *e3 = nullptr, *d2 = nullptr, *d1 = nullptr, *d0 = nullptr;
+    uint8_t* mask[NCONV - 1] = {};
+    uint16_t *gy = nullptr, *gd0 = nullptr, *gd1 = nullptr, *gd2 = nullptr, *ge3 = nullptr, *ge2 = nullptr,
+             *ge1 = nullptr, *ge0 = nullptr;
+    float *part = nullptr, *bpart = nullptr, *loss_part = nullptr;
     hipError_t err = hipSuccess;
 
     ~radon_cnn_s() {
-        for (void* p : allocs) (void)hipFree(p);
+        if (arena) (void)hipFree(arena);
     }
+    // Ask for `count` values; the pointers are set by allocate(), one device
+    // allocation for all of them (a hipMalloc each took most of the set-up).
     template <class T>
-    bool alloc(T** out, size_t count) {
-        void* p = nullptr;
-        if (hipMalloc(&p, sizeof(T) * std::max<size_t>(count, 1)) != hipSuccess) {
+    void want(T** out, size_t count) {
+        wanted.push_back({reinterpret_cast<void**>(out), bytes});
+        bytes += (sizeof(T) * std::max<size_t>(count, 1) + 255) / 256 * 256;
+    }
+    bool allocate() {
+        if (hipMalloc(&arena, bytes) != hipSuccess) {
             (void)hipGetLastError();
+            arena = nullptr;
             return false;
         }
-        allocs.push_back(p);
-        *out = static_cast<T*>(p);
+        for (auto& w : wanted) *w.first = static_cast<char*>(arena) + w.second;
         return true;
     }
     void chk(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
@@ -89,162 +117,171 @@ struct radon_cnn_s {
 namespace {
 
 size_t grid1(size_t n) { return std::min<size_t>((n + 255) / 256, 65535); }
-// chunks of k_conv3x3_wgrad for B images of h x w
-size_t wgrad_chunks(long long B, int h, int w) {
-    const long long tiles = B * (long long)((h + 7) / 8) * ((w + 7) / 8);
-    return (size_t)((tiles + cnn::WT_TILES - 1) / cnn::WT_TILES);
+int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+template <int CB, int TY, bool UP, int EPI>
+void conv_go(const cnn::ConvIn& a, const cnn::Epilogue& e, int B, hipStream_t st) {
+    const dim3 grid((unsigned)(B * cdiv(a.W, cnn::TX) * cdiv(a.H, TY)), (unsigned)(a.CoutP / CB));
+    hipLaunchKernelGGL((cnn::k_conv3x3<CB, TY, UP, EPI>), grid, dim3(CONV_NT), 0, st, a, e);
 }
 
-// k_conv3x3 over `cout` output channels: blocks of 64 channels on 8 x 8 pixel
-// tiles, or of 32 on 16 x 8 tiles when there are at most 32
-void conv_launch(const uint16_t* in, const uint16_t* Wg, int Kp, const float* bias, const uint16_t* res,
-                 const float* res32, uint16_t* out16, float* out32, int B, int cin, int cout, int h, int w, bool relu,
-                 hipStream_t st) {
-    auto tiles = [&](int tx) { return ((w + tx - 1) / tx) * ((h + cnn::CTY - 1) / cnn::CTY); };
-    if (cout <= 32) {
-        const dim3 grid((unsigned)(B * tiles(cnn::conv_tx(32))), 1u);
-        hipLaunchKernelGGL(cnn::k_conv3x3<32>, grid, dim3(CONV_NT), 0, st, in, Wg, Kp, bias, res, res32, out16,
-                           out32, B, cin, cout, h, w, relu ? 1 : 0);
+// Tile height by the workgroups it makes: tall tiles read the weights and the
+// window's border fewer times, but a workgroup per CU (256) has to be left.
+template <bool UP, int EPI>
+void conv_tile(const cnn::ConvIn& a, const cnn::Epilogue& e, int B, hipStream_t st) {
+    const int cb = a.CoutP % 64 == 0 ? 64 : 32;
+    auto groups = [&](int ty) { return (long long)B * cdiv(a.W, cnn::TX) * cdiv(a.H, ty) * (a.CoutP / cb); };
+    const int ty = groups(16) >= 512 ? 16 : (groups(8) >= 512 || cb == 32) ? 8 : 4;
+    if (cb == 64) {
+        if (ty == 16) conv_go<64, 16, UP, EPI>(a, e, B, st);
+        else if (ty == 8) conv_go<64, 8, UP, EPI>(a, e, B, st);
+        else conv_go<64, 4, UP, EPI>(a, e, B, st);
     } else {
-        const dim3 grid((unsigned)(B * tiles(cnn::conv_tx(64))), (unsigned)((cout + 63) / 64));
-        hipLaunchKernelGGL(cnn::k_conv3x3<64>, grid, dim3(CONV_NT), 0, st, in, Wg, Kp, bias, res, res32, out16,
-                           out32, B, cin, cout, h, w, relu ? 1 : 0);
+        if (ty == 16) conv_go<32, 16, UP, EPI>(a, e, B, st);
+        else conv_go<32, 8, UP, EPI>(a, e, B, st);
     }
 }
 
-void conv_fwd(radon_cnn_s& c, const Conv& L, const uint16_t* in, int h, int w, uint16_t* out16, float* out32,
-              const uint16_t* res, bool relu, hipStream_t st, const float* res32 = nullptr) {
-    conv_launch(in, L.Wg, L.Kp, L.b, res, res32, out16, out32, c.B, L.cin, L.cout, h, w, relu, st);
+cnn::ConvIn conv_in(const uint16_t* in, const uint8_t* mask, const Packed& w, int cin, int h, int ww) {
+    return cnn::ConvIn{reinterpret_cast<const uint4*>(in), mask, reinterpret_cast<const uint4*>(w.p),
+                       pad_to(cin, 16) / 8, w.rows, h, ww};
 }
 
-// data gradient: gin = conv(gout, flipped transposed kernel), no bias
-void conv_dgrad(radon_cnn_s& c, const Conv& L, const uint16_t* gout, int h, int w, uint16_t* gin, hipStream_t st) {
-    conv_launch(gout, L.Wt, L.Kpt, nullptr, nullptr, nullptr, gin, nullptr, c.B, L.cout, L.cin, h, w, false, st);
+// act = relu(conv(in) + bias) with the epilogue EPI_ACT; up: `in` is half the
+// size and read as its nearest upsampling
+void conv_act(radon_cnn_s& c, const Conv& L, const uint16_t* in, bool up, int h, int w, uint16_t* out, uint8_t* mask,
+              uint16_t* pool, const uint16_t* skip, hipStream_t st) {
+    const cnn::ConvIn a = conv_in(in, nullptr, L.fwd, L.cin, h, w);
+    const cnn::Epilogue e{L.b, 1, out, mask, pool, skip, nullptr, nullptr};
+    if (up) conv_tile<true, cnn::EPI_ACT>(a, e, c.B, st);
+    else conv_tile<false, cnn::EPI_ACT>(a, e, c.B, st);
 }
 
-void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* gout, const uint16_t* in, int h, int w, hipStream_t st) {
-    const long long np = (long long)c.B * h * w;
-    const int chunks = (int)wgrad_chunks(c.B, h, w);
-    const int K = L.cin * 9;
-    const dim3 grid((unsigned)chunks, (unsigned)((K + 63) / 64), (unsigned)((L.cout + 63) / 64));
-    hipLaunchKernelGGL(cnn::k_conv3x3_wgrad, grid, dim3(256), 0, st, gout, in, c.part, c.B, L.cin, L.cout, h, w);
-    hipLaunchKernelGGL(cnn::k_sum_chunks, dim3((unsigned)grid1(L.nw())), dim3(256), 0, st, c.part, chunks, L.nw(),
-                       L.gw);
-    // the bias partials reuse the weight partials' buffer, which the sum above has read
-    const int bchunks = (int)((np + cnn::BG_CHUNK - 1) / cnn::BG_CHUNK);
-    hipLaunchKernelGGL(cnn::k_bias_grad, dim3((unsigned)bchunks, (unsigned)L.cout), dim3(256), 0, st, gout, c.B,
-                       L.cout, h * w, c.part);
-    hipLaunchKernelGGL(cnn::k_sum_chunks, dim3((unsigned)grid1((size_t)L.cout)), dim3(256), 0, st, c.part, bchunks,
-                       (size_t)L.cout, L.gb);
+// data gradient through the layer and the upsampling before it
+void dgrad_up(radon_cnn_s& c, const Conv& L, const uint16_t* g, const uint8_t* gmask, int h, int w, uint16_t* out,
+              hipStream_t st) {
+    const cnn::Epilogue e{nullptr, 0, out, nullptr, nullptr, nullptr, nullptr, nullptr};
+    conv_tile<false, cnn::EPI_SUM4>(conv_in(g, gmask, L.dgr, L.cout, h, w), e, c.B, st);
+}
+
+// data gradient through the layer, the pooling before it and the ReLU (mask)
+// before that, joined by the gradient `skip` of the same activation
+void dgrad_pool(radon_cnn_s& c, const Conv& L, const uint16_t* g, const uint8_t* gmask, int h, int w,
+                const uint16_t* skip, uint8_t* mask, uint16_t* out, hipStream_t st) {
+    const cnn::Epilogue e{nullptr, 0, out, mask, nullptr, skip, nullptr, nullptr};
+    conv_tile<false, cnn::EPI_POOLG>(conv_in(g, gmask, L.dgr, L.cout, h, w), e, c.B, st);
+}
+
+template <class T, int EPI>
+void conv_c1(const T* in, const Packed& w, const cnn::Epilogue& e, int B, int h, int ww, hipStream_t st) {
+    hipLaunchKernelGGL((cnn::k_conv3x3_c1<T, EPI>), dim3((unsigned)(B * cdiv(h, 16) * cdiv(ww, 16))), dim3(CONV_NT), 0,
+                       st, in, reinterpret_cast<const uint4*>(w.p), h, ww, e);
+}
+
+// the one output channel of a layer: out = conv(in) + bias + res (float32)
+void conv_one(const uint16_t* in, const Packed& w, int cin, const float* bias, const float* res, float* out, int B, int h,
+              int ww, hipStream_t st) {
+    const cnn::Epilogue e{bias, 0, nullptr, nullptr, nullptr, nullptr, out, res};
+    conv_tile<false, cnn::EPI_ONE>(conv_in(in, nullptr, w, cin, h, ww), e, B, st);
+}
+
+// chunks of the weight and bias gradients for B images of h x w
+size_t wgrad_chunks(long long B, int h, int w) {
+    const long long tiles = B * (long long)cdiv(h, 8) * cdiv(w, 8);
+    return (size_t)((tiles + cnn::WG_TILES - 1) / cnn::WG_TILES);
+}
+size_t bias_chunks(long long B, int h, int w) { return (size_t)((B * h * w + cnn::BG_CHUNK - 1) / cnn::BG_CHUNK); }
+
+template <int COB, int CIB>
+void wgrad_go(const cnn::WgradArgs& a, int chunks, bool up, hipStream_t st) {
+    const dim3 grid((unsigned)chunks, (unsigned)cdiv(a.Cin, CIB), (unsigned)cdiv(a.Cout, COB));
+    constexpr int NT = cnn::wgrad_threads(COB, CIB);
+    if (up) hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, true>), grid, dim3(NT), 0, st, a);
+    else hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, false>), grid, dim3(NT), 0, st, a);
+}
+
+void sum_chunks(const float* part, size_t chunks, size_t n, int taps, float* out, hipStream_t st) {
+    hipLaunchKernelGGL(cnn::k_sum_chunks, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, (int)chunks, (int)n, taps,
+                       out);
+}
+
+// Weight and bias gradients of a layer at size h x w; x1: the single-channel
+// input of a layer with one (float32 or bf16)
+template <class T>
+void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* g, const uint8_t* gmask, const uint16_t* in, const T* x1, bool up,
+                int h, int w, hipStream_t st) {
+    const size_t chunks = wgrad_chunks(c.B, h, w), bchunks = bias_chunks(c.B, h, w);
+    const uint4* gp = reinterpret_cast<const uint4*>(g);
+    if (L.cin == 1 && L.cout == 32) {
+        hipLaunchKernelGGL((cnn::k_conv3x3_wgrad_c1<T, false>), dim3((unsigned)chunks), dim3(256), 0, st, gp, x1, c.B, h, w,
+                           c.part);
+    } else if (L.cin == 32 && L.cout == 1) {
+        hipLaunchKernelGGL((cnn::k_conv3x3_wgrad_c1<uint16_t, true>), dim3((unsigned)chunks), dim3(256), 0, st,
+                           reinterpret_cast<const uint4*>(in), g, c.B, h, w, c.part);
+    } else {
+        const cnn::WgradArgs a{gp, gmask, reinterpret_cast<const uint4*>(in), pad_to(L.cout, 16) / 8, pad_to(L.cin, 16) / 8,
+                               c.B, h, w, L.cout, L.cin, c.part};
+        // 64 x 64 channels per workgroup read each tile the fewest times; smaller
+        // blocks where those would leave CUs without a workgroup
+        if (L.cout % 64 == 0 && L.cin % 64 == 0 && chunks * (L.cout / 64) * (L.cin / 64) >= 256)
+            wgrad_go<64, 64>(a, (int)chunks, up, st);
+        else if (L.cin % 64 == 0 && chunks * cdiv(L.cout, 32) * (L.cin / 64) >= 256) wgrad_go<32, 64>(a, (int)chunks, up, st);
+        else wgrad_go<32, 32>(a, (int)chunks, up, st);
+    }
+    sum_chunks(c.part, chunks, L.nw(), 9, L.gw, st);
+    if (L.cin == 32 && L.cout == 1) {
+        hipLaunchKernelGGL(cnn::k_bias_grad1, dim3((unsigned)bchunks), dim3(256), 0, st, g, (long long)c.B * h * w, h * w,
+                           c.bpart);
+    } else {
+        hipLaunchKernelGGL(cnn::k_bias_grad, dim3((unsigned)bchunks, (unsigned)cdiv(L.cout, 8)), dim3(256), 0, st, gp, gmask,
+                           c.B, L.cout, pad_to(L.cout, 16) / 8, h * w, c.bpart);
+    }
+    sum_chunks(c.bpart, bchunks, (size_t)L.cout, 1, L.gb, st);
 }
 
 void pack(Conv& L, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_pack_weights, dim3(64), dim3(256), 0, st, L.w, L.cin, L.cout, L.Kp, L.Kpt, L.Wg, L.Wt);
-}
-
-void pool(const uint16_t* in, uint16_t* out, int bc, int h, int w, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_pool2, dim3((unsigned)grid1((size_t)bc * h * w / 4)), dim3(256), 0, st, in, out, bc, h, w);
-}
-void pool_grad(const uint16_t* gout, uint16_t* gin, int bc, int h, int w, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_pool2_grad, dim3((unsigned)grid1((size_t)bc * h * w)), dim3(256), 0, st, gout, gin, bc,
-                       h, w);
-}
-void up(const uint16_t* in, uint16_t* out, int bc, int h, int w, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_up2, dim3((unsigned)grid1((size_t)bc * 4 * h * w)), dim3(256), 0, st, in, out, bc, h, w);
-}
-void up_grad(const uint16_t* gout, uint16_t* gin, int bc, int h, int w, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_up2_grad, dim3((unsigned)grid1((size_t)bc * h * w)), dim3(256), 0, st, gout, gin, bc, h,
-                       w);
-}
-void relu_grad(const uint16_t* g, const uint16_t* act, const uint16_t* add, uint16_t* out, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_relu_grad, dim3((unsigned)grid1(n)), dim3(256), 0, st, g, act, add, out, n);
-}
-void add(const uint16_t* a, const uint16_t* b, uint16_t* out, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_add, dim3((unsigned)grid1(n)), dim3(256), 0, st, a, b, out, n);
+    hipLaunchKernelGGL(cnn::k_pack_weights, dim3((unsigned)grid1(L.fwd.count + L.dgr.count)), dim3(256), 0, st, L.w, L.cin,
+                       L.cout, L.fwd.layout, L.fwd.rows, (int)L.fwd.count, L.dgr.layout, L.dgr.rows, (int)L.dgr.count,
+                       L.fwd.p, L.dgr.p);
 }
 
 // forward of the whole network; y32 gets the float32 output
 void forward(radon_cnn_s& c, const float* x, float* y32, hipStream_t st) {
     const int B = c.B, H = c.H, W = c.W;
-    const size_t n0 = (size_t)B * H * W;
-    hipLaunchKernelGGL(cnn::k_to_bf16, dim3((unsigned)grid1(n0)), dim3(256), 0, st, x, c.x16, n0);
-    conv_fwd(c, c.conv[0], c.x16, H, W, c.e0, nullptr, nullptr, true, st);
-    pool(c.e0, c.p0, B * 32, H, W, st);
-    conv_fwd(c, c.conv[1], c.p0, H / 2, W / 2, c.e1, nullptr, nullptr, true, st);
-    pool(c.e1, c.p1, B * 64, H / 2, W / 2, st);
-    conv_fwd(c, c.conv[2], c.p1, H / 4, W / 4, c.e2, nullptr, nullptr, true, st);
-    pool(c.e2, c.p2, B * 128, H / 4, W / 4, st);
-    conv_fwd(c, c.conv[3], c.p2, H / 8, W / 8, c.e3, nullptr, nullptr, true, st);
-    up(c.e3, c.u3, B * 256, H / 8, W / 8, st);
-    conv_fwd(c, c.conv[4], c.u3, H / 4, W / 4, c.re, nullptr, nullptr, true, st);
-    add(c.re, c.e2, c.d2, (size_t)B * 128 * (H / 4) * (W / 4), st);
-    up(c.d2, c.u2, B * 128, H / 4, W / 4, st);
-    conv_fwd(c, c.conv[5], c.u2, H / 2, W / 2, c.rf, nullptr, nullptr, true, st);
-    add(c.rf, c.e1, c.d1, (size_t)B * 64 * (H / 2) * (W / 2), st);
-    up(c.d1, c.u1, B * 64, H / 2, W / 2, st);
-    conv_fwd(c, c.conv[6], c.u1, H, W, c.rg, nullptr, nullptr, true, st);
-    add(c.rg, c.e0, c.d0, (size_t)B * 32 * H * W, st);
-    conv_fwd(c, c.conv[7], c.d0, H, W, nullptr, y32, nullptr, false, st, x);   // + the float32 input
+    conv_c1<float, cnn::EPI_ACT>(x, c.conv[0].fwd, cnn::Epilogue{c.conv[0].b, 1, c.e0, c.mask[0], c.p0, nullptr, nullptr, nullptr},
+                                 B, H, W, st);
+    conv_act(c, c.conv[1], c.p0, false, H / 2, W / 2, c.e1, c.mask[1], c.p1, nullptr, st);
+    conv_act(c, c.conv[2], c.p1, false, H / 4, W / 4, c.e2, c.mask[2], c.p2, nullptr, st);
+    conv_act(c, c.conv[3], c.p2, false, H / 8, W / 8, c.e3, c.mask[3], nullptr, nullptr, st);
+    conv_act(c, c.conv[4], c.e3, true, H / 4, W / 4, c.d2, c.mask[4], nullptr, c.e2, st);
+    conv_act(c, c.conv[5], c.d2, true, H / 2, W / 2, c.d1, c.mask[5], nullptr, c.e1, st);
+    conv_act(c, c.conv[6], c.d1, true, H, W, c.d0, c.mask[6], nullptr, c.e0, st);
+    conv_one(c.d0, c.conv[7].fwd, 32, c.conv[7].b, x, y32, B, H, W, st);   // + the float32 input
 }
 
-// backward from gy (bf16 gradient of the output); fills every layer's gw, gb
-void backward(radon_cnn_s& c, hipStream_t st) {
+// backward from gy (bf16 gradient of the output; x: the network's input);
+// fills every layer's gw, gb. gd0, gd1, gd2, ge3 are the gradients of the
+// activations d0, d1, d2, e3 (masked by a layer's ReLU where it reads them),
+// ge2, ge1, ge0 those before the ReLUs of e2, e1, e0.
+void backward(radon_cnn_s& c, const float* x, hipStream_t st) {
     const int B = c.B, H = c.H, W = c.W;
-    const size_t s0 = (size_t)B * H * W, s1 = s0 / 4, s2 = s0 / 16, s3 = s0 / 64;
-    uint16_t *ga = c.ga, *gb = c.gb, *gc = c.gc;
-    // y = conv_h(d0) + x
-    conv_wgrad(c, c.conv[7], c.gy, c.d0, H, W, st);
-    conv_dgrad(c, c.conv[7], c.gy, H, W, ga, st);                         // ga = dL/dd0 (32 @ H)
-    // d0 = relu(conv_g(u1)) + e0: keep dL/de0 (skip part) in ga, pre-activation in gb
-    relu_grad(ga, c.rg, nullptr, gb, 32 * s0, st);
-    conv_wgrad(c, c.conv[6], gb, c.u1, H, W, st);
-    conv_dgrad(c, c.conv[6], gb, H, W, gc, st);                           // gc = dL/du1 (64 @ H)
-    up_grad(gc, gb, B * 64, H / 2, W / 2, st);                            // gb = dL/dd1 (64 @ H/2)
-    // d1 = relu(conv_f(u2)) + e1 (ga holds dL/de0 until the end; gb is dL/dd1)
-    uint16_t* gd1 = gb;
-    uint16_t* tmp = gc;
-    relu_grad(gd1, c.rf, nullptr, tmp, 64 * s1, st);
-    conv_wgrad(c, c.conv[5], tmp, c.u2, H / 2, W / 2, st);
-    uint16_t* gu2 = tmp + 64 * s1;                                         // after the pre-activation grad
-    conv_dgrad(c, c.conv[5], tmp, H / 2, W / 2, gu2, st);                 // 128 @ H/2
-    uint16_t* gd2 = gu2 + 128 * s1;
-    up_grad(gu2, gd2, B * 128, H / 4, W / 4, st);                         // 128 @ H/4
-    // d2 = relu(conv_e(u3)) + e2
-    uint16_t* tre = gd2 + 128 * s2;
-    relu_grad(gd2, c.re, nullptr, tre, 128 * s2, st);
-    conv_wgrad(c, c.conv[4], tre, c.u3, H / 4, W / 4, st);
-    uint16_t* gu3 = tre + 128 * s2;
-    conv_dgrad(c, c.conv[4], tre, H / 4, W / 4, gu3, st);                 // 256 @ H/4
-    uint16_t* ge3 = gu3 + 256 * s2;
-    up_grad(gu3, ge3, B * 256, H / 8, W / 8, st);                         // 256 @ H/8
-    // e3 = relu(conv_d(p2))
-    uint16_t* td = ge3 + 256 * s3;
-    relu_grad(ge3, c.e3, nullptr, td, 256 * s3, st);
-    conv_wgrad(c, c.conv[3], td, c.p2, H / 8, W / 8, st);
-    uint16_t* gp2 = td + 256 * s3;
-    conv_dgrad(c, c.conv[3], td, H / 8, W / 8, gp2, st);                  // 128 @ H/8
-    uint16_t* ge2p = gp2 + 128 * s3;
-    pool_grad(gp2, ge2p, B * 128, H / 4, W / 4, st);                      // 128 @ H/4
-    // e2 = relu(conv_c(p1)), total gradient = skip (gd2) + pooled path
-    uint16_t* tc = ge2p + 128 * s2;
-    relu_grad(gd2, c.e2, ge2p, tc, 128 * s2, st);
-    conv_wgrad(c, c.conv[2], tc, c.p1, H / 4, W / 4, st);
-    uint16_t* gp1 = tc + 128 * s2;
-    conv_dgrad(c, c.conv[2], tc, H / 4, W / 4, gp1, st);                  // 64 @ H/4
-    uint16_t* ge1p = gp1 + 64 * s2;
-    pool_grad(gp1, ge1p, B * 64, H / 2, W / 2, st);                       // 64 @ H/2
-    // e1 = relu(conv_b(p0)), total = skip (gd1) + pooled path
-    uint16_t* tb = ge1p + 64 * s1;
-    relu_grad(gd1, c.e1, ge1p, tb, 64 * s1, st);
-    conv_wgrad(c, c.conv[1], tb, c.p0, H / 2, W / 2, st);
-    uint16_t* gp0 = tb + 64 * s1;
-    conv_dgrad(c, c.conv[1], tb, H / 2, W / 2, gp0, st);                  // 32 @ H/2
-    uint16_t* ge0p = gp0 + 32 * s1;
-    pool_grad(gp0, ge0p, B * 32, H, W, st);                               // 32 @ H
-    // e0 = relu(conv_a(x)), total = skip (ga) + pooled path
-    uint16_t* ta = ge0p + 32 * s0;
-    relu_grad(ga, c.e0, ge0p, ta, 32 * s0, st);
-    conv_wgrad(c, c.conv[0], ta, c.x16, H, W, st);
+    const uint16_t* none = nullptr;
+    conv_wgrad(c, c.conv[7], c.gy, nullptr, c.d0, none, false, H, W, st);
+    conv_c1<uint16_t, cnn::EPI_ACT>(c.gy, c.conv[7].dgr, cnn::Epilogue{nullptr, 0, c.gd0, nullptr, nullptr, nullptr, nullptr, nullptr},
+                                    B, H, W, st);
+    conv_wgrad(c, c.conv[6], c.gd0, c.mask[6], c.d1, none, true, H, W, st);
+    dgrad_up(c, c.conv[6], c.gd0, c.mask[6], H, W, c.gd1, st);
+    conv_wgrad(c, c.conv[5], c.gd1, c.mask[5], c.d2, none, true, H / 2, W / 2, st);
+    dgrad_up(c, c.conv[5], c.gd1, c.mask[5], H / 2, W / 2, c.gd2, st);
+    conv_wgrad(c, c.conv[4], c.gd2, c.mask[4], c.e3, none, true, H / 4, W / 4, st);
+    dgrad_up(c, c.conv[4], c.gd2, c.mask[4], H / 4, W / 4, c.ge3, st);
+    conv_wgrad(c, c.conv[3], c.ge3, c.mask[3], c.p2, none, false, H / 8, W / 8, st);
+    dgrad_pool(c, c.conv[3], c.ge3, c.mask[3], H / 8, W / 8, c.gd2, c.mask[2], c.ge2, st);
+    conv_wgrad(c, c.conv[2], c.ge2, nullptr, c.p1, none, false, H / 4, W / 4, st);
+    dgrad_pool(c, c.conv[2], c.ge2, nullptr, H / 4, W / 4, c.gd1, c.mask[1], c.ge1, st);
+    conv_wgrad(c, c.conv[1], c.ge1, nullptr, c.p0, none, false, H / 2, W / 2, st);
+    dgrad_pool(c, c.conv[1], c.ge1, nullptr, H / 2, W / 2, c.gd0, c.mask[0], c.ge0, st);
+    conv_wgrad(c, c.conv[0], c.ge0, nullptr, none, x, false, H, W, st);
 }
 
 }  // namespace
@@ -268,21 +305,44 @@ radon_status_t radon_cnn_create(radon_cnn_t* out, int batch, int height, int wid
     c->H = height;
     c->W = width;
     const int chans[NCONV][2] = {{1, 32}, {32, 64}, {64, 128}, {128, 256}, {256, 128}, {128, 64}, {64, 32}, {32, 1}};
-    std::mt19937_64 rng(seed);
-    bool ok = true;
-    size_t part_n = 0;
+    size_t part_n = 0, bpart_n = 0;
     const int sizes[NCONV] = {1, 2, 4, 8, 4, 2, 1, 1};   // spatial divisor of each layer
-    for (int l = 0; l < NCONV && ok; ++l) {
+    for (int l = 0; l < NCONV; ++l) {
         Conv& L = c->conv[l];
         L.cin = chans[l][0];
         L.cout = chans[l][1];
-        L.Kp = pad8(L.cin * 9);
-        L.Kpt = pad8(L.cout * 9);
+        L.fwd = packed_for(L.cin, L.cout);
+        L.dgr = packed_for(L.cout, L.cin);
+        if (l == 0) L.dgr.count = 0;   // the input needs no gradient
+        for (float** p : {&L.w, &L.gw, &L.mw, &L.vw}) c->want(p, L.nw());
+        for (float** p : {&L.b, &L.gb, &L.mb, &L.vb}) c->want(p, L.cout);
+        c->want(&L.fwd.p, L.fwd.count);
+        c->want(&L.dgr.p, L.dgr.count);
+        part_n = std::max(part_n, wgrad_chunks(batch, height / sizes[l], width / sizes[l]) * L.nw());
+        bpart_n = std::max(bpart_n, bias_chunks(batch, height / sizes[l], width / sizes[l]) * L.cout);
+    }
+    const size_t s0 = (size_t)batch * height * width, s1 = s0 / 4, s2 = s0 / 16, s3 = s0 / 64;
+    const size_t acts[NCONV - 1] = {32 * s0, 64 * s1, 128 * s2, 256 * s3, 128 * s2, 64 * s1, 32 * s0};
+    for (int l = 0; l < NCONV - 1; ++l) c->want(&c->mask[l], acts[l] / 8);
+    for (uint16_t** p : {&c->e0, &c->d0, &c->gd0, &c->ge0}) c->want(p, 32 * s0);
+    for (uint16_t** p : {&c->e1, &c->d1, &c->gd1, &c->ge1}) c->want(p, 64 * s1);
+    for (uint16_t** p : {&c->e2, &c->d2, &c->gd2, &c->ge2}) c->want(p, 128 * s2);
+    for (uint16_t** p : {&c->e3, &c->ge3}) c->want(p, 256 * s3);
+    c->want(&c->p0, 32 * s1);
+    c->want(&c->p1, 64 * s2);
+    c->want(&c->p2, 128 * s3);
+    c->want(&c->gy, s0);
+    c->want(&c->part, part_n);
+    c->want(&c->bpart, bpart_n);
+    c->want(&c->loss_part, 1024);
+    if (!c->allocate()) {
+        delete c;
+        return errf(RADON_ERR_OOM, "device allocation failed");
+    }
+    std::mt19937_64 rng(seed);
+    for (int l = 0; l < NCONV; ++l) {
+        Conv& L = c->conv[l];
         const size_t nw = L.nw();
-        ok = c->alloc(&L.w, nw) && c->alloc(&L.b, L.cout) && c->alloc(&L.gw, nw) && c->alloc(&L.gb, L.cout) &&
-             c->alloc(&L.mw, nw) && c->alloc(&L.vw, nw) && c->alloc(&L.mb, L.cout) && c->alloc(&L.vb, L.cout) &&
-             c->alloc(&L.Wg, (size_t)L.cout * L.Kp) && c->alloc(&L.Wt, (size_t)L.cin * L.Kpt);
-        if (!ok) break;
         // He initialisation (the last layer starts at zero: the network begins as the identity)
         std::vector<float> w(nw), zb(L.cout, 0.f), z(nw, 0.f);
         std::normal_distribution<float> nd(0.f, sqrtf(2.0f / (L.cin * 9)));
@@ -292,24 +352,6 @@ radon_status_t radon_cnn_create(radon_cnn_t* out, int batch, int height, int wid
         for (float* p : {L.mw, L.vw}) c->chk(hipMemcpy(p, z.data(), sizeof(float) * nw, hipMemcpyHostToDevice));
         for (float* p : {L.mb, L.vb}) c->chk(hipMemcpy(p, zb.data(), sizeof(float) * L.cout, hipMemcpyHostToDevice));
         pack(L, 0);
-        const size_t chunks = wgrad_chunks(batch, height / sizes[l], width / sizes[l]);
-        part_n = std::max(part_n, chunks * nw);
-    }
-    const size_t s0 = (size_t)batch * height * width, s1 = s0 / 4, s2 = s0 / 16, s3 = s0 / 64;
-    ok = ok && c->alloc(&c->x16, s0) && c->alloc(&c->e0, 32 * s0) && c->alloc(&c->p0, 32 * s1) &&
-         c->alloc(&c->e1, 64 * s1) && c->alloc(&c->p1, 64 * s2) && c->alloc(&c->e2, 128 * s2) &&
-         c->alloc(&c->p2, 128 * s3) && c->alloc(&c->e3, 256 * s3) && c->alloc(&c->u3, 256 * s2) &&
-         c->alloc(&c->re, 128 * s2) && c->alloc(&c->d2, 128 * s2) && c->alloc(&c->u2, 128 * s1) &&
-         c->alloc(&c->rf, 64 * s1) && c->alloc(&c->d1, 64 * s1) && c->alloc(&c->u1, 64 * s0) &&
-         c->alloc(&c->rg, 32 * s0) && c->alloc(&c->d0, 32 * s0) && c->alloc(&c->gy, s0) &&
-         c->alloc(&c->ga, 32 * s0) && c->alloc(&c->gb, 64 * s0) &&
-         c->alloc(&c->gc, 64 * s0 + 64 * s1 + 128 * s1 + 4 * 128 * s2 + 2 * 256 * s2 + 3 * 256 * s3 +
-                              2 * 128 * s3 + 64 * s2 + 3 * 64 * s1 + 32 * s1 + 2 * 32 * s0) &&
-         c->alloc(&c->part, part_n) && c->alloc(&c->loss_part, 1024);
-    c->part_n = part_n;
-    if (!ok) {
-        delete c;
-        return errf(RADON_ERR_OOM, "device allocation failed");
     }
     c->chk(hipDeviceSynchronize());
     if (c->err != hipSuccess) {
@@ -340,7 +382,7 @@ radon_status_t radon_cnn_train_step(radon_cnn_t net, const float* in_dev, const 
     forward(c, in_dev, pred_dev, st);
     const int nblk = (int)std::min<size_t>((n0 + 255) / 256, 1024);
     hipLaunchKernelGGL(cnn::k_mse, dim3(nblk), dim3(256), 0, st, pred_dev, target_dev, n0, c.gy, c.loss_part);
-    backward(c, st);
+    backward(c, in_dev, st);
     // Adam
     c.step += 1;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
@@ -421,20 +463,51 @@ radon_status_t radon_cnn_conv_test(const uint16_t* in, const float* w, const flo
     Conv L;
     L.cin = Cin;
     L.cout = Cout;
-    L.Kp = pad8(Cin * 9);
-    L.Kpt = pad8(Cout * 9);
+    L.fwd = packed_for(Cin, Cout);
+    L.dgr = packed_for(Cout, Cin);
     L.w = const_cast<float*>(w);
-    L.b = const_cast<float*>(bias);
     L.gw = gw;
     L.gb = gb;
-    const size_t chunks = wgrad_chunks(B, H, W);
-    if (!c.alloc(&L.Wg, (size_t)Cout * L.Kp) || !c.alloc(&L.Wt, (size_t)Cin * L.Kpt) ||
-        !c.alloc(&c.part, chunks * L.nw()))
+    const int HW = H * W, Pi = pad_to(Cin, 16) / 8, Po = pad_to(Cout, 16) / 8;
+    const int Cs = std::max(pad_to(Cin, 32), pad_to(Cout, 32));
+    uint16_t *xp = nullptr, *gp = nullptr;   // the tensors in planes (one channel: as they are)
+    float* sums = nullptr;
+    c.want(&L.fwd.p, L.fwd.count);
+    c.want(&L.dgr.p, L.dgr.count);
+    c.want(&c.part, wgrad_chunks(B, H, W) * L.nw());
+    c.want(&c.bpart, bias_chunks(B, H, W) * Cout);
+    c.want(&xp, (size_t)B * Pi * HW * 8);
+    c.want(&gp, (size_t)B * Po * HW * 8);
+    c.want(&sums, (size_t)B * Cs * HW);
+    if (!c.allocate())
         return errf(RADON_ERR_OOM, "test buffers");
+    auto planes = [&](const uint16_t* src, uint16_t* dst, int C, int P) {
+        hipLaunchKernelGGL(cnn::k_to_planes, dim3((unsigned)grid1((size_t)B * P * HW * 8)), dim3(256), 0, st, src, dst, B, C,
+                           P, HW);
+    };
+    // the sums of a convolution of ci into co channels, then [relu](sums + bias) [+ res]
+    auto convolve = [&](const uint16_t* nchw, const uint16_t* in, const Packed& pk, int ci, int co, const float* bi,
+                        const uint16_t* re, int act, uint16_t* o16, float* o32) {
+        const cnn::Epilogue e{nullptr, 0, nullptr, nullptr, nullptr, nullptr, sums, nullptr};
+        int P = pk.rows / 8;
+        if (pk.layout == cnn::WL_C1) {
+            conv_c1<uint16_t, cnn::EPI_F32>(nchw, pk, e, B, H, W, st);
+            P = 4;
+        } else if (co == 1) {
+            conv_one(in, pk, ci, nullptr, nullptr, sums, B, H, W, st);
+            P = 0;
+        } else {
+            conv_tile<false, cnn::EPI_F32>(conv_in(in, nullptr, pk, ci, H, W), e, B, st);
+        }
+        hipLaunchKernelGGL(cnn::k_from_sums, dim3((unsigned)grid1((size_t)B * co * HW)), dim3(256), 0, st, sums, bi, re, act,
+                           o16, o32, B, co, P, HW);
+    };
     pack(L, st);
-    if (out16 || out32) conv_fwd(c, L, in, H, W, out16, out32, res, relu != 0, st);
-    if (gout && gin) conv_dgrad(c, L, gout, H, W, gin, st);
-    if (gout && gw && gb) conv_wgrad(c, L, gout, in, H, W, st);
+    planes(in, xp, Cin, Pi);
+    if (out16 || out32) convolve(in, xp, L.fwd, Cin, Cout, bias, res, relu != 0, out16, out32);
+    if (gout) planes(gout, gp, Cout, Po);
+    if (gout && gin) convolve(gout, gp, L.dgr, Cout, Cin, nullptr, nullptr, 0, gin, nullptr);
+    if (gout && gw && gb) conv_wgrad(c, L, Cout == 1 && Cin == 32 ? gout : gp, nullptr, xp, in, false, H, W, st);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
         return errf(RADON_ERR_DEVICE, "convolution test failed");
     return rn::api_ok();
