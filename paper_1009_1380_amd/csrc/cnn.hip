@@ -125,20 +125,24 @@ void conv_go(const cnn::ConvIn& a, const cnn::Epilogue& e, int B, hipStream_t st
     hipLaunchKernelGGL((cnn::k_conv3x3<CB, TY, UP, EPI>), grid, dim3(CONV_NT), 0, st, a, e);
 }
 
-// Tile height by the workgroups it makes: tall tiles read the weights and the
-// window's border fewer times, but a workgroup per CU (256) has to be left.
+// Channel blocks of 64 (32 for layers with 32) and the tile height by the
+// workgroups it makes: tall tiles read the weights and the window's border
+// fewer times, but two workgroups per CU (512) have to be left. Blocks of 32
+// channels take 8 rows, which hold more workgroups per CU (32 -> 1 channel at
+// 512 x 512, batch 8: 89 us against 116 with 16 rows), but 16 on an upsampled
+// input, whose window is small (64 -> 32: 158 against 164 us).
 template <bool UP, int EPI>
 void conv_tile(const cnn::ConvIn& a, const cnn::Epilogue& e, int B, hipStream_t st) {
     const int cb = a.CoutP % 64 == 0 ? 64 : 32;
     auto groups = [&](int ty) { return (long long)B * cdiv(a.W, cnn::TX) * cdiv(a.H, ty) * (a.CoutP / cb); };
-    const int ty = groups(16) >= 512 ? 16 : (groups(8) >= 512 || cb == 32) ? 8 : 4;
     if (cb == 64) {
-        if (ty == 16) conv_go<64, 16, UP, EPI>(a, e, B, st);
-        else if (ty == 8) conv_go<64, 8, UP, EPI>(a, e, B, st);
+        if (groups(16) >= 512) conv_go<64, 16, UP, EPI>(a, e, B, st);
+        else if (groups(8) >= 512) conv_go<64, 8, UP, EPI>(a, e, B, st);
         else conv_go<64, 4, UP, EPI>(a, e, B, st);
+    } else if (UP && groups(16) >= 512) {
+        conv_go<32, UP ? 16 : 8, UP, EPI>(a, e, B, st);
     } else {
-        if (ty == 16) conv_go<32, 16, UP, EPI>(a, e, B, st);
-        else conv_go<32, 8, UP, EPI>(a, e, B, st);
+        conv_go<32, 8, UP, EPI>(a, e, B, st);
     }
 }
 
