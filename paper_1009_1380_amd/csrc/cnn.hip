@@ -66,7 +66,6 @@ struct Conv {
     int cin = 0, cout = 0;
     float *w = nullptr, *b = nullptr;          // parameters (float32)
     float *gw = nullptr, *gb = nullptr;        // gradients
-    float *mw = nullptr, *vw = nullptr, *mb = nullptr, *vb = nullptr;   // Adam moments
     Packed fwd, dgr;                           // bf16 operands (forward, data gradient)
     size_t nw() const { return (size_t)cout * cin * 9; }
 };
@@ -80,6 +79,8 @@ struct radon_cnn_s {
     int B = 0, H = 0, W = 0;
     int step = 0;
     Conv conv[NCONV];
+    // parameters, gradients and Adam moments, each in layer order (weights, biases)
+    float *params = nullptr, *grads = nullptr, *mom = nullptr, *var = nullptr;
     void* arena = nullptr;                               // all device memory
     std::vector<std::pair<void**, size_t>> wanted;       // what it will hold: pointer, offset
     size_t bytes = 0;
@@ -196,17 +197,13 @@ size_t wgrad_chunks(long long B, int h, int w) {
 }
 size_t bias_chunks(long long B, int h, int w) { return (size_t)((B * h * w + cnn::BG_CHUNK - 1) / cnn::BG_CHUNK); }
 
-template <int COB, int CIB>
+constexpr int WGRAD_FLIGHT = 2;   // tiles in flight (1 and 3 are no faster; 3 costs registers)
+template <int COB, int CIB, int TW, int WD = WGRAD_FLIGHT>
 void wgrad_go(const cnn::WgradArgs& a, int chunks, bool up, hipStream_t st) {
     const dim3 grid((unsigned)chunks, (unsigned)cdiv(a.Cin, CIB), (unsigned)cdiv(a.Cout, COB));
-    constexpr int NT = cnn::wgrad_threads(COB, CIB);
-    if (up) hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, true>), grid, dim3(NT), 0, st, a);
-    else hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, false>), grid, dim3(NT), 0, st, a);
-}
-
-void sum_chunks(const float* part, size_t chunks, size_t n, int taps, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(cnn::k_sum_chunks, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, (int)chunks, (int)n, taps,
-                       out);
+    constexpr int NT = cnn::wgrad_threads(COB, CIB, TW);
+    if (up) hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, TW, true, WD>), grid, dim3(NT), 0, st, a);
+    else hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, TW, false, WD>), grid, dim3(NT), 0, st, a);
 }
 
 // Weight and bias gradients of a layer at size h x w; x1: the single-channel
@@ -228,11 +225,10 @@ void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* g, const uint8_t* gmask
         // 64 x 64 channels per workgroup read each tile the fewest times; smaller
         // blocks where those would leave CUs without a workgroup
         if (L.cout % 64 == 0 && L.cin % 64 == 0 && chunks * (L.cout / 64) * (L.cin / 64) >= 256)
-            wgrad_go<64, 64>(a, (int)chunks, up, st);
-        else if (L.cin % 64 == 0 && chunks * cdiv(L.cout, 32) * (L.cin / 64) >= 256) wgrad_go<32, 64>(a, (int)chunks, up, st);
-        else wgrad_go<32, 32>(a, (int)chunks, up, st);
+            wgrad_go<64, 64, 3>(a, (int)chunks, up, st);
+        else if (L.cin % 64 == 0 && chunks * cdiv(L.cout, 32) * (L.cin / 64) >= 256) wgrad_go<32, 64, 3>(a, (int)chunks, up, st);
+        else wgrad_go<32, 32, 1>(a, (int)chunks, up, st);
     }
-    sum_chunks(c.part, chunks, L.nw(), 9, L.gw, st);
     if (L.cin == 32 && L.cout == 1) {
         hipLaunchKernelGGL(cnn::k_bias_grad1, dim3((unsigned)bchunks), dim3(256), 0, st, g, (long long)c.B * h * w, h * w,
                            c.bpart);
@@ -240,7 +236,9 @@ void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* g, const uint8_t* gmask
         hipLaunchKernelGGL(cnn::k_bias_grad, dim3((unsigned)bchunks, (unsigned)cdiv(L.cout, 8)), dim3(256), 0, st, gp, gmask,
                            c.B, L.cout, pad_to(L.cout, 16) / 8, h * w, c.bpart);
     }
-    sum_chunks(c.bpart, bchunks, (size_t)L.cout, 1, L.gb, st);
+    const int nw = (int)L.nw(), wblocks = cdiv(nw, 32);
+    hipLaunchKernelGGL(cnn::k_sum_chunks, dim3((unsigned)(wblocks + cdiv(L.cout, 32))), dim3(256), 0, st, c.part,
+                       (int)chunks, nw, L.gw, wblocks, c.bpart, (int)bchunks, L.cout, L.gb);
 }
 
 void pack(Conv& L, hipStream_t st) {
@@ -318,13 +316,13 @@ radon_status_t radon_cnn_create(radon_cnn_t* out, int batch, int height, int wid
         L.fwd = packed_for(L.cin, L.cout);
         L.dgr = packed_for(L.cout, L.cin);
         if (l == 0) L.dgr.count = 0;   // the input needs no gradient
-        for (float** p : {&L.w, &L.gw, &L.mw, &L.vw}) c->want(p, L.nw());
-        for (float** p : {&L.b, &L.gb, &L.mb, &L.vb}) c->want(p, L.cout);
         c->want(&L.fwd.p, L.fwd.count);
         c->want(&L.dgr.p, L.dgr.count);
         part_n = std::max(part_n, wgrad_chunks(batch, height / sizes[l], width / sizes[l]) * L.nw());
         bpart_n = std::max(bpart_n, bias_chunks(batch, height / sizes[l], width / sizes[l]) * L.cout);
     }
+    const size_t np = (size_t)radon_cnn_param_count(c);
+    for (float** p : {&c->params, &c->grads, &c->mom, &c->var}) c->want(p, np);
     const size_t s0 = (size_t)batch * height * width, s1 = s0 / 4, s2 = s0 / 16, s3 = s0 / 64;
     const size_t acts[NCONV - 1] = {32 * s0, 64 * s1, 128 * s2, 256 * s3, 128 * s2, 64 * s1, 32 * s0};
     for (int l = 0; l < NCONV - 1; ++l) c->want(&c->mask[l], acts[l] / 8);
@@ -343,20 +341,26 @@ radon_status_t radon_cnn_create(radon_cnn_t* out, int batch, int height, int wid
         delete c;
         return errf(RADON_ERR_OOM, "device allocation failed");
     }
+    // He initialisation (the last layer starts at zero: the network begins as the identity)
     std::mt19937_64 rng(seed);
+    std::vector<float> init(np, 0.f);
+    size_t at = 0;
     for (int l = 0; l < NCONV; ++l) {
         Conv& L = c->conv[l];
-        const size_t nw = L.nw();
-        // He initialisation (the last layer starts at zero: the network begins as the identity)
-        std::vector<float> w(nw), zb(L.cout, 0.f), z(nw, 0.f);
         std::normal_distribution<float> nd(0.f, sqrtf(2.0f / (L.cin * 9)));
-        for (auto& v : w) v = (l == NCONV - 1) ? 0.f : nd(rng);
-        c->chk(hipMemcpy(L.w, w.data(), sizeof(float) * nw, hipMemcpyHostToDevice));
-        c->chk(hipMemcpy(L.b, zb.data(), sizeof(float) * L.cout, hipMemcpyHostToDevice));
-        for (float* p : {L.mw, L.vw}) c->chk(hipMemcpy(p, z.data(), sizeof(float) * nw, hipMemcpyHostToDevice));
-        for (float* p : {L.mb, L.vb}) c->chk(hipMemcpy(p, zb.data(), sizeof(float) * L.cout, hipMemcpyHostToDevice));
-        pack(L, 0);
+        if (l < NCONV - 1)
+            for (size_t k = 0; k < L.nw(); ++k) init[at + k] = nd(rng);
+        L.w = c->params + at;
+        L.gw = c->grads + at;
+        at += L.nw();
+        L.b = c->params + at;
+        L.gb = c->grads + at;
+        at += L.cout;
     }
+    c->chk(hipMemcpy(c->params, init.data(), sizeof(float) * np, hipMemcpyHostToDevice));
+    std::fill(init.begin(), init.end(), 0.f);
+    for (float* p : {c->mom, c->var}) c->chk(hipMemcpy(p, init.data(), sizeof(float) * np, hipMemcpyHostToDevice));
+    for (Conv& L : c->conv) pack(L, 0);
     c->chk(hipDeviceSynchronize());
     if (c->err != hipSuccess) {
         delete c;
@@ -391,14 +395,16 @@ radon_status_t radon_cnn_train_step(radon_cnn_t net, const float* in_dev, const 
     c.step += 1;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.f - powf(b1, (float)c.step), c2 = 1.f - powf(b2, (float)c.step);
+    cnn::UpdateArgs u{};
+    int at = 0;
     for (int l = 0; l < NCONV; ++l) {
-        Conv& L = c.conv[l];
-        hipLaunchKernelGGL(cnn::k_adam, dim3((unsigned)grid1(L.nw())), dim3(256), 0, st, L.w, L.gw, L.mw, L.vw,
-                           L.nw(), lr, b1, b2, eps, c1, c2);
-        hipLaunchKernelGGL(cnn::k_adam, dim3(1), dim3(256), 0, st, L.b, L.gb, L.mb, L.vb, (size_t)L.cout, lr, b1, b2,
-                           eps, c1, c2);
-        pack(L, st);
+        const Conv& L = c.conv[l];
+        u.layer[l] = {at, L.cin, L.cout, L.fwd.p, L.fwd.layout, L.fwd.rows, L.dgr.count ? L.dgr.p : nullptr, L.dgr.layout,
+                      L.dgr.rows};
+        at += (int)L.nw() + L.cout;
     }
+    hipLaunchKernelGGL(cnn::k_update, dim3((unsigned)cdiv(at, 256)), dim3(256), 0, st, u, c.params, c.grads, c.mom, c.var, at,
+                       lr, b1, b2, eps, c1, c2);
     if (hipGetLastError() != hipSuccess) return errf(RADON_ERR_DEVICE, "training step launch failed");
     if (loss_host) {
         std::vector<float> part(nblk);
@@ -425,25 +431,15 @@ int64_t radon_cnn_param_count(radon_cnn_t net) {
 static radon_status_t copy_params(radon_cnn_t net, float* host, int64_t n, bool grads, bool to_device) {
     if (!net || !host) return errf(RADON_ERR_INVALID, "NULL argument");
     if (n != radon_cnn_param_count(net)) return errf(RADON_ERR_INVALID, "need %lld values", (long long)radon_cnn_param_count(net));
-    size_t off = 0;
-    for (Conv& L : net->conv) {
-        float* w = grads ? L.gw : L.w;
-        float* b = grads ? L.gb : L.b;
-        hipError_t e;
-        if (to_device) {
-            e = hipMemcpy(w, host + off, sizeof(float) * L.nw(), hipMemcpyHostToDevice);
-            if (e == hipSuccess) e = hipMemcpy(b, host + off + L.nw(), sizeof(float) * L.cout, hipMemcpyHostToDevice);
-            pack(L, 0);
-        } else {
-            e = hipMemcpy(host + off, w, sizeof(float) * L.nw(), hipMemcpyDeviceToHost);
-            if (e == hipSuccess) e = hipMemcpy(host + off + L.nw(), b, sizeof(float) * L.cout, hipMemcpyDeviceToHost);
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return errf(RADON_ERR_DEVICE, "parameter copy failed");
-        }
-        off += L.nw() + L.cout;
+    float* dev = grads ? net->grads : net->params;
+    const hipError_t e = to_device ? hipMemcpy(dev, host, sizeof(float) * n, hipMemcpyHostToDevice)
+                                   : hipMemcpy(host, dev, sizeof(float) * n, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return errf(RADON_ERR_DEVICE, "parameter copy failed");
     }
+    if (to_device)
+        for (Conv& L : net->conv) pack(L, 0);
     if (hipDeviceSynchronize() != hipSuccess) return errf(RADON_ERR_DEVICE, "parameter copy failed");
     return rn::api_ok();
 }

@@ -447,28 +447,50 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(6))) vo
 // does not depend on how the channels and taps are spread over waves.
 //
 // A workgroup takes COB output x CIB input channels of one chunk; each wave
-// takes 32 x 32 channels and the three taps of one kernel row. Operands are
-// four pixels of one channel, so the pieces (eight channels of one pixel) are
-// transposed two pixels at a time in registers on their way to LDS. A lane's
-// input row is the six pixels around its four (one 16-byte read); the operands
-// of the taps left and right of the centre are dword pairs of it, the centre's
-// two funnel shifts. The next tile's loads are in flight during the products.
-// Channels sit at a swizzled place (wg_pos), so that the transposed writes
-// spread over the banks.
-// Measured (64 -> 32 channels at 512 x 512, batch 8, 77 GFLOP): 169 us against
-// 1191 us with 2-byte operand reads and one tile in flight; 256 -> 128 at 128 x
-// 128: 144 against 511 us.
+// takes 32 x 32 channels and the three taps of one kernel column. A lane's
+// operand is four pixels of one channel, while a piece is eight channels of one
+// pixel: ds_read_b64_tr_b16 transposes on the way out of LDS (tr_at), so that
+// pieces are staged as they are, the loads run along the pixels of a row, and a
+// tap is only another address. A wave reads its 8 gradient and 10 input rows
+// once per tile for 24 matrix instructions. WD tiles are in flight during the
+// products. Blocks of 32 x 32 channels, for layers whose chunks are few, run
+// with one tap per wave: with three waves on a CU the products waited for each
+// other (1260 cycles per tile where the instructions take 770).
+// Measured at batch 8, 512 x 512: 64 -> 32 channels (77 GFLOP) 142 us, 128 -> 64
+// 116, 256 -> 128 116; 1191, 572 and 511 us with 2-byte operand reads and one
+// tile in flight, 169, 152 and 144 with the transposition in registers, whose
+// loads touched one cache line per lane.
 // Grid: x = chunks, y = blocks of CIB input channels, z = of COB output channels.
 constexpr int WG_TILES = 64;
 
-__device__ __forceinline__ int wg_pos(int c) { return (c & ~7) | ((c & 7) ^ ((c >> 3) & 7)); }
-
-// Channel c of the pieces of two neighbouring pixels.
-__device__ __forceinline__ uint32_t pair_of(uint4 p, uint4 q, int c) {
-    const uint32_t a = c < 2 ? p.x : c < 4 ? p.y : c < 6 ? p.z : p.w;
-    const uint32_t d = c < 2 ? q.x : c < 4 ? q.y : c < 6 ? q.z : q.w;
-    return __builtin_amdgcn_perm(d, a, (c & 1) ? 0x07060302u : 0x05040100u);
+// Transposing LDS read: of the 16 lanes of a group, lane j asks for 8 bytes (four
+// values) of row j / 4, and receives value j of the concatenated four chunks of
+// each of the rows 0..3. Lane j of a 32-channel operand therefore asks for pixel
+// j / 4 of the lane half's four, channels 4 (j % 4) .. of the group's sixteen:
+// tr_at gives the byte offset in planes `stride` bytes apart.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ __forceinline__ int tr_at(int lane, int stride) {
+    const int j = lane & 15, kh = lane >> 5, q = (lane >> 4) & 1;
+    return (2 * q + ((j & 3) >> 1)) * stride + (4 * kh + (j >> 2)) * 16 + (j & 1) * 8;
 }
+__device__ __forceinline__ uint2 read_tr(const void* p) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+}
+
+// Place of an 8 x 8 tile: image and top left pixel; tiles in row order.
+struct TileAt {
+    int b, y, x;
+    __device__ static TileAt of(int t, int H, int W) {
+        const int tx = (W + 7) / 8, n = tx * ((H + 7) / 8), r = t % n;
+        return TileAt{t / n, r / tx * 8, r % tx * 8};
+    }
+    __device__ void next(int H, int W) {
+        x += 8;
+        if (x >= W) { x = 0; y += 8; }
+        if (y >= H) { y = 0; ++b; }
+    }
+};
 
 struct WgradArgs {
     const uint4* g;          // gradient pieces, Pg planes
@@ -478,255 +500,273 @@ struct WgradArgs {
     float* part;
 };
 
-constexpr int wgrad_threads(int cob, int cib) { return cob / 32 * (cib / 32) * 3 * 64; }
+// Pieces of a staged plane: 8 x 8 of the gradient, 10 x 10 of the input; the
+// distance of planes in LDS is a quarter of the banks past a full turn, so the
+// four planes that half a wave reads together do not conflict.
+constexpr int WG_GS = 68, WG_XS = 100;
 
-template <int COB, int CIB, bool UP>
-__global__ __launch_bounds__(wgrad_threads(COB, CIB)) void k_conv3x3_wgrad(WgradArgs a) {
-    constexpr int NT = wgrad_threads(COB, CIB);
-    constexpr int NG = COB / 8 * 8 * 4, NX = CIB / 8 * 10 * 5;   // pixel pairs: planes x rows x pairs
-    constexpr int RU = (NG + NX + NT - 1) / NT;
-    constexpr int GROW = COB * 4, XROW = 2 * CIB * 4;            // dwords per tile row
-    __shared__ __align__(16) uint32_t sh[2][8 * GROW + 10 * XROW];
+// TW: taps of a wave, the three of a kernel column or one.
+constexpr int wgrad_threads(int cob, int cib, int tw) { return cob / 32 * (cib / 32) * (9 / tw) * 64; }
+
+template <int COB, int CIB, int TW, bool UP, int WD>
+__global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(WgradArgs a) {
+    constexpr int NT = wgrad_threads(COB, CIB, TW);
+    constexpr int NG = COB / 8 * 64, NX = CIB / 8 * 100, RU = (NG + NX + NT - 1) / NT;
+    constexpr int GP = COB / 8 * WG_GS, XP = CIB / 8 * WG_XS;   // pieces of a buffer
+    __shared__ uint4 sh[2][GP + XP];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles_x = (a.W + 7) / 8, tiles = tiles_x * ((a.H + 7) / 8);
-    const int ntiles = a.B * tiles;
+    const int ntiles = a.B * ((a.W + 7) / 8) * ((a.H + 7) / 8);
     const int cb = blockIdx.z * COB, ib = blockIdx.y * CIB;
-    const int Hi = UP ? a.H / 2 : a.H, Wi = UP ? a.W / 2 : a.W;
+    constexpr int us = UP ? 1 : 0;
+    const int Hi = a.H >> us, Wi = a.W >> us;
 
-    // this thread's pixel pairs: gradient rows 0..7, pixels 2 pr, 2 pr + 1; input
-    // rows -1..8, pixels 2 pr - 1, 2 pr
-    int upl[RU], urow[RU], upr[RU];
+    // this thread's pieces: place in LDS (-1: none), offset from the tile's first
+    // pixel (input: from one row and column before it), row and column in the tile
+    int at[RU], row[RU], col[RU];
+    unsigned off[RU];
     bool isg[RU], has[RU];
 #pragma unroll
     for (int k = 0; k < RU; ++k) {
         const int e = tid + k * NT;
         isg[k] = e < NG;
-        const int u = isg[k] ? e : e - NG, np = isg[k] ? COB / 8 : CIB / 8, npr = isg[k] ? 4 : 5;
-        upl[k] = u % np;
-        upr[k] = (u / np) % npr;
-        urow[k] = u / np / npr;
-        has[k] = e < NG + NX;
+        const int u = isg[k] ? e : e - NG;
+        const int pl = isg[k] ? u / 64 : u / 100, r = isg[k] ? u % 64 : u % 100;
+        row[k] = isg[k] ? r / 8 : r / 10 - 1;
+        col[k] = isg[k] ? r % 8 : r % 10 - 1;
+        const int plane = (isg[k] ? cb : ib) / 8 + pl;
+        at[k] = e < NG + NX ? (isg[k] ? pl * WG_GS + r : GP + pl * WG_XS + r) : -1;
+        has[k] = e < NG + NX && plane < (isg[k] ? a.Pg : a.Pi);
+        off[k] = !has[k] ? 0u : (unsigned)(isg[k] ? (plane * a.H + row[k]) * a.W + col[k]
+                                                  : (plane * Hi + (row[k] >> us) + 1) * Wi + (col[k] >> us) + 1);
     }
-    uint4 v[RU][2];
-    unsigned mk[RU][2] = {};
-    auto load = [&](int t) {
-        const int b = t / tiles, tr = t - b * tiles;
-        const int y0 = (tr / tiles_x) * 8, x0 = (tr - (tr / tiles_x) * tiles_x) * 8;
+    uint4 vr[WD][RU];
+    unsigned mr[WD][RU] = {};
+    auto load = [&](const TileAt& t, uint4 (&v)[RU], unsigned (&mk)[RU]) {
+        const ptrdiff_t gb = ((ptrdiff_t)t.b * a.Pg * a.H + t.y) * a.W + t.x;
+        const uint4* gp = a.g + gb;
+        const uint4* xp = a.in + (((ptrdiff_t)t.b * a.Pi * Hi + (t.y >> us) - 1) * Wi + (t.x >> us) - 1);
+        const bool inner = t.y > 0 && t.x > 0 && t.y + 8 < a.H && t.x + 8 < a.W;   // uniform
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
-            const int plane = (isg[k] ? cb : ib) / 8 + upl[k], y = y0 + urow[k] - (isg[k] ? 0 : 1);
-            const bool ok = has[k] && plane < (isg[k] ? a.Pg : a.Pi) && y >= 0 && y < a.H;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int x = x0 + 2 * upr[k] + j - (isg[k] ? 0 : 1);
-                v[k][j] = make_uint4(0u, 0u, 0u, 0u);
-                if (ok && x >= 0 && x < a.W) {
-                    if (isg[k]) {
-                        const size_t o = (((size_t)b * a.Pg + plane) * a.H + y) * a.W + x;
-                        v[k][j] = a.g[o];
-                        if (a.gmask) mk[k][j] = a.gmask[o];
-                    } else {
-                        v[k][j] = a.in[(((size_t)b * a.Pi + plane) * Hi + (UP ? y >> 1 : y)) * Wi + (UP ? x >> 1 : x)];
-                    }
-                }
+            const int y = t.y + row[k], x = t.x + col[k];
+            v[k] = make_uint4(0u, 0u, 0u, 0u);
+            if (has[k] && (inner || (y >= 0 && y < a.H && x >= 0 && x < a.W))) {
+                v[k] = (isg[k] ? gp : xp)[off[k]];
+                if (a.gmask && isg[k]) mk[k] = a.gmask[gb + off[k]];
             }
         }
     };
-    auto store = [&](uint32_t* buf) {
+    auto store = [&](uint4* buf, const uint4 (&v)[RU], const unsigned (&mk)[RU]) {
 #pragma unroll
-        for (int k = 0; k < RU; ++k) {
-            if (!has[k]) continue;
-            if (isg[k]) {
-                // [row pair][half][channel] pieces: the four pixels of the pair's rows
-                if (a.gmask) {
-                    v[k][0] = mask_piece(v[k][0], mk[k][0]);
-                    v[k][1] = mask_piece(v[k][1], mk[k][1]);
-                }
-                uint32_t* d = buf + ((urow[k] >> 1) * 2 + (upr[k] >> 1)) * COB * 4 + (urow[k] & 1) * 2 + (upr[k] & 1);
-#pragma unroll
-                for (int c = 0; c < 8; ++c) d[wg_pos(upl[k] * 8 + c) * 4] = pair_of(v[k][0], v[k][1], c);
-            } else {
-                // [row][half][channel] pieces: pairs 0..2 to half 0, 2..4 to half 1
-                uint32_t* d = buf + 8 * GROW + urow[k] * XROW;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const uint32_t p = pair_of(v[k][0], v[k][1], c);
-                    const int at = wg_pos(upl[k] * 8 + c) * 4;
-                    if (upr[k] <= 2) d[at + upr[k]] = p;
-                    if (upr[k] >= 2) d[CIB * 4 + at + upr[k] - 2] = p;
-                }
-            }
-        }
+        for (int k = 0; k < RU; ++k)
+            if (at[k] >= 0) buf[at[k]] = a.gmask && isg[k] ? mask_piece(v[k], mk[k]) : v[k];
     };
 
     const int i = lane & 31, kh = lane >> 5;
-    const int dy = wave % 3, wmn = wave / 3, wm = wmn % (COB / 32), wn = wmn / (COB / 32);
-    const int go = kh * COB * 4 + wg_pos(wm * 32 + i) * 4;
-    const int xo = 8 * GROW + dy * XROW + kh * CIB * 4 + wg_pos(wn * 32 + i) * 4;
-    f32x16 acc[3] = {};
+    // the wave's kernel column and (first) kernel row, and its 32 x 32 channels
+    const int dx = wave % 3, dy = TW == 3 ? 0 : wave / 3 % 3;
+    const int wmn = wave / (9 / TW), wm = wmn % (COB / 32), wn = wmn / (COB / 32);
+    const int go = wm * 4 * WG_GS * 16 + tr_at(lane, WG_GS * 16);
+    const int xo = (GP + wn * 4 * WG_XS + dy * 10 + dx) * 16 + tr_at(lane, WG_XS * 16);
+    f32x16 acc[TW] = {};
     const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
-    load(t0);
-    store(sh[0]);
-    lds_sync();
-    for (int t = t0; t < t1; ++t) {
-        if (t + 1 < t1) load(t + 1);
-        const uint32_t* buf = sh[(t - t0) & 1];
-        uint4 ga;
+    TileAt cur = TileAt::of(t0, a.H, a.W);   // the next tile to load
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            if (r % 2 == 0) ga = *reinterpret_cast<const uint4*>(buf + go + (r >> 1) * 2 * COB * 4);
-            const uint32_t a0 = r % 2 ? ga.z : ga.x, a1 = r % 2 ? ga.w : ga.y;
-            const uint4 q = *reinterpret_cast<const uint4*>(buf + xo + r * XROW);
-            acc[0] = mfma(a0, a1, q.x, q.y, acc[0]);
-            acc[1] = mfma(a0, a1, __builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16), acc[1]);
-            acc[2] = mfma(a0, a1, q.y, q.z, acc[2]);
+    for (int d = 0; d < WD; ++d)
+        if (t0 + d < t1) {
+            load(cur, vr[d], mr[d]);
+            cur.next(a.H, a.W);
         }
-        if (t + 1 < t1) store(sh[(t + 1 - t0) & 1]);
-        lds_sync();
+    store(sh[0], vr[0], mr[0]);
+    lds_sync();
+    for (int tb = t0; tb < t1; tb += WD) {
+#pragma unroll
+        for (int d = 0; d < WD; ++d) {   // slot d of the ring held tile t = tb + d, which is in LDS
+            const int t = tb + d;
+            if (t >= t1) break;   // uniform
+            if (t + WD < t1) {
+                load(cur, vr[d], mr[d]);
+                cur.next(a.H, a.W);
+            }
+            const char* buf = reinterpret_cast<const char*>(sh[(t - t0) & 1]);
+            uint2 ga[8], gx[7 + TW];
+#pragma unroll
+            for (int r = 0; r < 7 + TW; ++r) {
+                if (r < 8) ga[r] = read_tr(buf + go + r * 128);
+                gx[r] = read_tr(buf + xo + r * 160);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int y = 0; y < TW; ++y) acc[y] = mfma(ga[r].x, ga[r].y, gx[r + y].x, gx[r + y].y, acc[y]);
+            if (t + 1 < t1) store(sh[(t + 1 - t0) & 1], vr[(d + 1) % WD], mr[(d + 1) % WD]);
+            lds_sync();
+        }
     }
     const int ci = ib + wn * 32 + i;
-    float* dst = a.part + ((size_t)blockIdx.x * 9 + 3 * dy) * a.Cout * a.Cin;
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
+    for (int y = 0; y < TW; ++y) {
+        float* dst = a.part + ((size_t)blockIdx.x * 9 + 3 * (y + dy) + dx) * a.Cout * a.Cin;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int co = cb + wm * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
-            if (co < a.Cout && ci < a.Cin) dst[((size_t)t * a.Cout + co) * a.Cin + ci] = acc[t][r];
+            if (co < a.Cout && ci < a.Cin) dst[(size_t)co * a.Cin + ci] = acc[y][r];
         }
+    }
 }
 
 // Weight gradient between a 32-channel tensor g and a single channel s:
 //   part[chunk][tap][c] = sum over the chunk's pixels p of g[c][p] s[p + off],
 // off the tap's offset; with FLIP s is the gradient and g the layer's input,
 // and the sum is over s[p] g[c][p + off]. The same tiles, chunks and order as
-// k_conv3x3_wgrad. The taps are the columns of the products (their rows with
-// FLIP the channels' shifted pixels), nine of 32. One wave per workgroup
-// computes, all four transpose; bound by reading g. Grid: x = chunks.
+// k_conv3x3_wgrad. The taps are the columns of the products (with FLIP the
+// shifted pixels of g are, and s is their one row). Bound by reading g: TB tiles
+// are staged at a time, the next TB in flight; one wave (with FLIP three)
+// computes. Grid: x = chunks.
 template <class T, bool FLIP>
 __global__ __launch_bounds__(256) void k_conv3x3_wgrad_c1(const uint4* __restrict__ g, const T* __restrict__ s, int B,
                                                          int H, int W, float* __restrict__ part) {
-    // GX: columns of g staged per tile row, 8 (or 10 with FLIP, whose channels are read shifted)
-    constexpr int GR = FLIP ? 10 : 8, NP = FLIP ? 5 : 4, NU = 4 * GR * NP;   // rows, pixel pairs, units
-    constexpr int SR = FLIP ? 8 : 10;                                         // rows and columns of s
-    __shared__ __align__(16) uint32_t sg[2][GR * 2 * 32 * 4];
-    __shared__ __align__(16) uint16_t ss[2][SR * SR];
+    constexpr int GR = FLIP ? 10 : 8, GS = FLIP ? WG_XS : WG_GS;   // rows and columns of g, its planes' distance
+    constexpr int SR = FLIP ? 8 : 10, NS = SR * SR;                // rows and columns of s
+    constexpr int TB = FLIP ? 3 : 4;
+    constexpr int NU = 4 * GR * GR, RU = (NU + 255) / 256;   // pieces of a tile, per thread
+    __shared__ uint4 sg[2][TB * 4 * GS];
+    __shared__ __align__(16) uint16_t ss[2][TB * NS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles_x = (W + 7) / 8, tiles = tiles_x * ((H + 7) / 8), ntiles = B * tiles;
-    const int upl = tid & 3, upr = (tid >> 2) % NP, row = (tid >> 2) / NP;
-    const bool has = tid < NU;
-    uint4 v[2];
-    T sv = (T)0;
-    auto load = [&](int t) {
-        const int b = t / tiles, tr = t - b * tiles;
-        const int y0 = (tr / tiles_x) * 8, x0 = (tr - (tr / tiles_x) * tiles_x) * 8;
-        const int y = y0 + row - (FLIP ? 1 : 0);
+    const int ntiles = B * ((W + 7) / 8) * ((H + 7) / 8);
+    const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
+    // this thread's pieces of a tile and its value of s: place, row and column
+    constexpr int gd = FLIP ? 1 : 0, sd = FLIP ? 0 : 1;      // border of g, of s
+    int at[RU], row[RU], col[RU];
+    unsigned off[RU];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int x = x0 + 2 * upr + j - (FLIP ? 1 : 0);
-            v[j] = (has && y >= 0 && y < H && x >= 0 && x < W) ? g[(((size_t)b * 4 + upl) * H + y) * W + x]
-                                                              : make_uint4(0u, 0u, 0u, 0u);
+    for (int k = 0; k < RU; ++k) {
+        const int e = tid + 256 * k, pl = e / (GR * GR), r = e - pl * GR * GR;
+        row[k] = r / GR - gd;
+        col[k] = r % GR - gd;
+        at[k] = e < NU ? pl * GS + r : -1;
+        off[k] = e < NU ? (unsigned)((pl * H + row[k] + gd) * W + col[k] + gd) : 0u;
+    }
+    const int srow = tid / SR - sd, scol = tid % SR - sd;
+    const unsigned soff = (unsigned)((srow + sd) * W + scol + sd);
+    uint4 v[TB][RU];
+    T sv[TB];
+    TileAt cur = TileAt::of(t0, H, W);   // the next tile to load
+    auto load = [&](int t) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const uint4* gp = g + (((ptrdiff_t)cur.b * 4 * H + cur.y - gd) * W + cur.x - gd);
+            const T* sp = s + (((ptrdiff_t)cur.b * H + cur.y - sd) * W + cur.x - sd);
+            const bool live = t + b < t1;                                                                  // uniform
+            const bool inner = live && cur.y > 0 && cur.x > 0 && cur.y + 8 < H && cur.x + 8 < W;           // uniform
+            auto in = [&](int r, int c) {
+                const int y = cur.y + r, x = cur.x + c;
+                return inner || (live && y >= 0 && y < H && x >= 0 && x < W);
+            };
+#pragma unroll
+            for (int k = 0; k < RU; ++k)
+                v[b][k] = at[k] >= 0 && in(row[k], col[k]) ? gp[off[k]] : make_uint4(0u, 0u, 0u, 0u);
+            sv[b] = tid < NS && in(srow, scol) ? sp[soff] : (T)0;
+            cur.next(H, W);
         }
-        const int sy = y0 + tid / SR - (FLIP ? 0 : 1), sxx = x0 + tid % SR - (FLIP ? 0 : 1);
-        sv = (tid < SR * SR && sy >= 0 && sy < H && sxx >= 0 && sxx < W) ? s[((size_t)b * H + sy) * W + sxx] : (T)0;
     };
     auto store = [&](int p) {
-        if (has) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint32_t q = pair_of(v[0], v[1], c);
-                const int at = wg_pos(upl * 8 + c) * 4;
-                uint32_t* d = sg[p] + row * 256;
-                if (!FLIP) {
-                    d[(upr >> 1) * 128 + at + (upr & 1)] = q;
-                } else {
-                    if (upr <= 2) d[at + upr] = q;
-                    if (upr >= 2) d[128 + at + upr - 2] = q;
-                }
-            }
+        for (int b = 0; b < TB; ++b) {
+#pragma unroll
+            for (int k = 0; k < RU; ++k)
+                if (at[k] >= 0) sg[p][b * 4 * GS + at[k]] = v[b][k];
+            if (tid < NS) ss[p][b * NS + tid] = to_bits(sv[b]);
         }
-        if (tid < SR * SR) ss[p][tid] = to_bits(sv);
     };
     const int i = lane & 31, kh = lane >> 5;
-    const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
-    const int go = kh * 128 + wg_pos(i) * 4;
-    f32x16 acc[FLIP ? 9 : 1] = {};
+    const int go = tr_at(lane, GS * 16) + (FLIP ? wave * 16 : 0);   // with FLIP wave = kernel column
+    const int so = i < 9 ? (i / 3) * 10 + i % 3 + 4 * kh : 0;
+    f32x16 acc[FLIP ? 3 : 1] = {};
     load(t0);
     store(0);
     lds_sync();
-    for (int t = t0; t < t1; ++t) {
-        if (t + 1 < t1) load(t + 1);
-        const uint32_t* bg = sg[(t - t0) & 1];
-        const uint16_t* bs = ss[(t - t0) & 1];
-        if (!FLIP) {
-            if (wave == 0) {
-                const int so = i < 9 ? (i / 3) * 10 + i % 3 + 4 * kh : 0;
+    for (int t = t0, p = 0; t < t1; t += TB, p ^= 1) {
+        if (t + TB < t1) load(t + TB);
+        if (wave < (FLIP ? 3 : 1)) {
+            for (int b = 0; b < TB && t + b < t1; ++b) {
+                const char* bg = reinterpret_cast<const char*>(&sg[p][b * 4 * GS]) + go;
+                const uint16_t* bs = ss[p] + b * NS;
+                if constexpr (!FLIP) {
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const uint2 ga = *reinterpret_cast<const uint2*>(bg + r * 256 + go);
-                    const uint32_t d0 = bs[r * 10 + so] | ((uint32_t)bs[r * 10 + so + 1] << 16);
-                    const uint32_t d1 = bs[r * 10 + so + 2] | ((uint32_t)bs[r * 10 + so + 3] << 16);
-                    acc[0] = mfma(ga.x, ga.y, i < 9 ? d0 : 0u, i < 9 ? d1 : 0u, acc[0]);
+                    for (int r = 0; r < 8; ++r) {
+                        const uint2 ga = read_tr(bg + r * 128);
+                        const uint32_t d0 = bs[r * 10 + so] | ((uint32_t)bs[r * 10 + so + 1] << 16);
+                        const uint32_t d1 = bs[r * 10 + so + 2] | ((uint32_t)bs[r * 10 + so + 3] << 16);
+                        acc[0] = mfma(ga.x, ga.y, i < 9 ? d0 : 0u, i < 9 ? d1 : 0u, acc[0]);
+                    }
+                } else {
+                    uint2 gx[10];
+#pragma unroll
+                    for (int r = 0; r < 10; ++r) gx[r] = read_tr(bg + r * 160);
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const uint2 q = *reinterpret_cast<const uint2*>(bs + r * 8 + 4 * kh);
+                        const uint32_t a0 = i == 0 ? q.x : 0u, a1 = i == 0 ? q.y : 0u;   // row 0 of 32
+#pragma unroll
+                        for (int y = 0; y < 3; ++y) acc[y] = mfma(a0, a1, gx[r + y].x, gx[r + y].y, acc[y]);
+                    }
                 }
             }
-        } else if (wave < 3) {
-            // rows: the one channel (row 0 of 32); wave = kernel row
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const uint32_t* q2 = reinterpret_cast<const uint32_t*>(bs + r * 8 + 4 * kh);
-                const uint32_t a0 = i == 0 ? q2[0] : 0u, a1 = i == 0 ? q2[1] : 0u;
-                const uint4 q = *reinterpret_cast<const uint4*>(bg + (r + wave) * 256 + go);
-                acc[0] = mfma(a0, a1, q.x, q.y, acc[0]);
-                acc[1] = mfma(a0, a1, __builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16), acc[1]);
-                acc[2] = mfma(a0, a1, q.y, q.z, acc[2]);
-            }
         }
-        if (t + 1 < t1) store((t + 1 - t0) & 1);
+        if (t + TB < t1) store(p ^ 1);
         lds_sync();
     }
     float* dst = part + (size_t)blockIdx.x * 288;
-    if (!FLIP) {
+    if constexpr (!FLIP) {
         if (wave == 0 && i < 9) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) dst[i * 32 + 8 * (r >> 2) + 4 * kh + (r & 3)] = acc[0][r];
         }
     } else if (wave < 3 && kh == 0) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t) dst[(3 * wave + t) * 32 + i] = acc[t][0];
+        for (int y = 0; y < 3; ++y) dst[(3 * y + wave) * 32 + i] = acc[y][0];
     }
 }
 
-// out[(co Cin + ci) 9 + tap] = sum over chunks, in order, of part[chunk][tap][co][ci]
-// (taps = 9), or out[e] = sum of part[chunk][e] (taps = 1). n: values per chunk.
-// A workgroup takes 32 values: its eight rows of threads load 8 chunks' values
-// at a time (eight loads in flight each) into LDS, the first row adds them in
-// order.
+// Sums over chunks, in order: workgroups below `wblocks` take the weights,
+//   out[(co Cin + ci) 9 + tap] = sum of part[chunk][tap][co][ci], n = 9 Cout Cin,
+// the others the biases, bout[e] = sum of bpart[chunk][e], nb of them. A
+// workgroup takes 32 values: its eight rows of threads load eight chunks each
+// at a time into LDS (one thread alone waits out a latency per few chunks), the
+// first row adds them in order.
 constexpr int SC_LD = 8;   // loads in flight per thread
-__global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ part, int chunks, int n, int taps,
-                                                   float* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ part, int chunks, int n,
+                                                   float* __restrict__ out, int wblocks, const float* __restrict__ bpart,
+                                                   int bchunks, int nb, float* __restrict__ bout) {
     __shared__ float sh[8 * SC_LD][33];
+    const bool bias = (int)blockIdx.x >= wblocks;
+    const float* src = bias ? bpart : part;
+    const int nc = bias ? bchunks : chunks, nv = bias ? nb : n;
     const int l = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int e = blockIdx.x * 32 + l;
+    const int e = ((int)blockIdx.x - (bias ? wblocks : 0)) * 32 + l;
     float s = 0.f;
-    for (int c0 = 0; c0 < chunks; c0 += 8 * SC_LD) {
+    for (int c0 = 0; c0 < nc; c0 += 8 * SC_LD) {
         float v[SC_LD];
 #pragma unroll
         for (int k = 0; k < SC_LD; ++k) {
             const int c = c0 + k * 8 + g;
-            v[k] = (c < chunks && e < n) ? part[(size_t)c * n + e] : 0.f;
+            v[k] = (c < nc && e < nv) ? src[(size_t)c * nv + e] : 0.f;
         }
 #pragma unroll
         for (int k = 0; k < SC_LD; ++k) sh[k * 8 + g][l] = v[k];
         __syncthreads();
         if (g == 0) {
-            const int m = min(8 * SC_LD, chunks - c0);
+            const int m = min(8 * SC_LD, nc - c0);
 #pragma unroll 16
             for (int k = 0; k < m; ++k) s += sh[k][l];
         }
         __syncthreads();
     }
-    if (g == 0 && e < n) {
-        const int per = n / taps, t = e / per;
-        out[(size_t)(e - t * per) * taps + t] = s;
+    if (g == 0 && e < nv) {
+        const int per = n / 9, t = e / per;
+        if (bias) bout[e] = s;
+        else out[(e - t * per) * 9 + t] = s;
     }
 }
 
@@ -737,45 +777,50 @@ __global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ pa
 // consecutive pairs of the eight channels of a plane per step; the values are
 // added two by two when H * W is a multiple of 8 (a step then never crosses an
 // image), else one by one. Grid: x = chunks, y = planes.
-constexpr int BG_CHUNK = 16384;   // pairs per chunk (a multiple of 256 * 8)
+constexpr int BG_CHUNK = 16384;   // pairs per chunk (a multiple of 256 * 16)
 __global__ __launch_bounds__(256) void k_bias_grad(const uint4* __restrict__ g, const uint8_t* __restrict__ mask, int B,
                                                   int C, int P, int HW, float* __restrict__ part) {
     __shared__ float sh[8][256];
     const int pl = blockIdx.y;
     const long long n = (long long)B * HW, q0 = (long long)blockIdx.x * BG_CHUNK;
+    const int b0 = (int)(q0 / HW);                       // the chunk starts at pixel p0 of image b0
+    const int p0 = (int)(q0 - (long long)b0 * HW);
+    const int left = (int)min((long long)BG_CHUNK, n - q0);
+    auto place = [&](int k) {                            // piece of pair q0 + k
+        const unsigned p = (unsigned)(p0 + k), b = p / (unsigned)HW;
+        return ((size_t)(b0 + b) * P + pl) * HW + (p - b * HW);
+    };
+    auto ch = [](const uint4& v, int c) {
+        const uint32_t d = c < 2 ? v.x : c < 4 ? v.y : c < 6 ? v.z : v.w;
+        return (c & 1) ? hi2f(d) : lo2f(d);
+    };
     float s[8] = {};
-    for (int k = threadIdx.x * 8; k < BG_CHUNK; k += 256 * 8) {
-        uint4 v[8];
-        unsigned m[8] = {};
+    if (HW % 8 == 0) {   // n and left are multiples of 8 too
+#pragma unroll 2
+        for (int k = threadIdx.x * 8; k < left; k += 256 * 8) {
+            const size_t o = place(k);
+            uint4 v[8];
+            uint2 m = make_uint2(0u, 0u);
+            if (mask) m = *reinterpret_cast<const uint2*>(mask + o);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const long long q = q0 + k + j;
-            v[j] = make_uint4(0u, 0u, 0u, 0u);
-            if (q < n) {
-                const int b = (int)(q / HW);
-                const size_t o = ((size_t)b * P + pl) * HW + (size_t)(q - (long long)b * HW);
-                v[j] = g[o];
-                if (mask) m[j] = mask[o];
+            for (int j = 0; j < 8; ++j) v[j] = g[o + j];
+            if (mask) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = mask_piece(v[j], (j < 4 ? m.x : m.y) >> (8 * (j & 3)));
             }
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) s[c] += ch(v[j], c) + ch(v[j + 1], c);
         }
-        if (mask) {
+    } else {
+        for (int k = threadIdx.x * 8; k < left; k += 256 * 8)
+            for (int j = 0; j < 8 && k + j < left; ++j) {
+                const size_t o = place(k + j);
+                const uint4 v = mask ? mask_piece(g[o], mask[o]) : g[o];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = mask_piece(v[j], m[j]);
-        }
-        auto ch = [&](int j, int c) {
-            const uint32_t d = c < 2 ? v[j].x : c < 4 ? v[j].y : c < 6 ? v[j].z : v[j].w;
-            return (c & 1) ? hi2f(d) : lo2f(d);
-        };
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            if (HW % 8 == 0) {
-#pragma unroll
-                for (int j = 0; j < 8; j += 2) s[c] += ch(j, c) + ch(j + 1, c);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) s[c] += ch(j, c);
+                for (int c = 0; c < 8; ++c) s[c] += ch(v, c);
             }
-        }
     }
 #pragma unroll
     for (int c = 0; c < 8; ++c) sh[c][threadIdx.x] = s[c];
@@ -904,17 +949,49 @@ __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ pred, con
     if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// Adam step on float32 parameters (bias-corrected, step count t >= 1).
-__global__ void k_adam(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, size_t n, float lr, float b1, float b2, float eps, float c1, float c2) {
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
-        const float ge = g[e];
-        const float me = b1 * m[e] + (1.f - b1) * ge;
-        const float ve = b2 * v[e] + (1.f - b2) * ge * ge;
-        m[e] = me;
-        v[e] = ve;
-        w[e] -= lr * (me / c1) / (sqrtf(ve / c2) + eps);
+// Place of value (row, reduction index, tap) in an operand layout.
+__device__ __forceinline__ size_t packed_at(int layout, int rowsP, int row, int red, int tap) {
+    if (layout == WL_CHUNK) {
+        const int k = (red & 15) * 9 + tap, S = k >> 3, h = (k >> 2) & 1;
+        return ((((size_t)(red >> 4) * 18 + (S >> 1) * 2 + h) * rowsP + row) << 3) + (S & 1) * 4 + (k & 3);
     }
+    return tap < 8 ? (((tap >> 2) * 32 + row) << 3) + (tap & 3) : (row << 3) + 4;
+}
+
+// Adam step on all float32 parameters (bias-corrected, step count >= 1), and the
+// new weights' bf16 operands (the padding of the layouts stays zero). One launch
+// for the network: 24 launches, one per tensor and packing, took 110 us.
+struct UpdateArgs {
+    struct Layer {
+        int first, cin, cout;            // its first parameter; weights, then biases
+        uint16_t* fwd;                   // operands of the forward ...
+        int lf, rf;                      // ... their layout and rows
+        uint16_t* dgr;                   // operands of the data gradient (null: none)
+        int ld, rd;
+    } layer[8];
+};
+__global__ __launch_bounds__(256) void k_update(UpdateArgs a, float* __restrict__ w, const float* __restrict__ g,
+                                               float* __restrict__ m, float* __restrict__ v, int n, float lr, float b1,
+                                               float b2, float eps, float c1, float c2) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    const float ge = g[e];
+    const float me = b1 * m[e] + (1.f - b1) * ge;
+    const float ve = b2 * v[e] + (1.f - b2) * ge * ge;
+    m[e] = me;
+    v[e] = ve;
+    const float we = w[e] - lr * (me / c1) / (sqrtf(ve / c2) + eps);
+    w[e] = we;
+    UpdateArgs::Layer L = a.layer[0];
+#pragma unroll
+    for (int l = 1; l < 8; ++l)
+        if (e >= a.layer[l].first) L = a.layer[l];
+    const int k = e - L.first;
+    if (k >= L.cout * L.cin * 9) return;   // a bias
+    const int tap = k % 9, cc = k / 9, ci = cc % L.cin, co = cc / L.cin;
+    const uint16_t h = f2bf(we);
+    L.fwd[packed_at(L.lf, L.rf, co, ci, tap)] = h;
+    if (L.dgr) L.dgr[packed_at(L.ld, L.rd, ci, co, 8 - tap)] = h;
 }
 
 }  // namespace cnn
