@@ -141,8 +141,11 @@ radon_status_t radon_adjoint(radon_plan_t plan, const float* sino_dev, float* im
  */
 radon_status_t radon_fbp(radon_plan_t plan, const float* sino_dev, float* img_dev, void* stream);
 
-/* batch slices that share the plan's geometry, back to back on the stream:
- * imgs_dev is batch*n*n float32, sinos_dev is batch*n_views*n_det float32. */
+/* batch slices that share the plan's geometry: imgs_dev is batch*n*n float32,
+ * sinos_dev is batch*n_views*n_det float32. Slices small enough to leave the
+ * device idle are taken several per pass; the workspace for that (at most 128
+ * MiB) is allocated by the first call that uses it and freed with the plan.
+ * Every slice's result equals its single call's bit for bit. */
 radon_status_t radon_forward_batched(radon_plan_t plan, int batch, const float* imgs_dev,
                                      float* sinos_dev, void* stream);
 radon_status_t radon_adjoint_batched(radon_plan_t plan, int batch, const float* sinos_dev,

@@ -5,15 +5,15 @@
 
 namespace rn {
 
-hipError_t launch_a1(const Plan& p, const float* sino, bool filtered, hipStream_t st) {
+hipError_t launch_a1(const Plan& p, const Work& w, const float* sino, bool filtered, hipStream_t st) {
     const float* wq = filtered ? p.fbpw : nullptr;
-    const dim3 grid((p.n_views + 1) / 2);
+    const dim3 grid((p.n_views + 1) / 2, w.slices);
     switch (p.n_det) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = ray_threads(L);                                                     \
-        hipLaunchKernelGGL((k_a1_rays<L, NT>), grid, dim3(NT), 0, st, sino, p.Yh, p.tw_N, wq,   \
-                           p.n_views);                                                         \
+        hipLaunchKernelGGL((k_a1_rays<L, NT>), grid, dim3(NT), 0, st, sino, w.Yh, p.tw_N, wq,   \
+                           p.n_views, w.sino_n, w.ray_n);                                      \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)
@@ -25,51 +25,57 @@ hipError_t launch_a1(const Plan& p, const float* sino, bool filtered, hipStream_
 }
 
 template <int W, int T>
-static hipError_t launch_a2_wt(const Plan& p, hipStream_t st) {
+static hipError_t launch_a2_wt(const Plan& p, const Work& w, hipStream_t st) {
     if (p.n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_a2_spread<W, T>), dim3(p.n_items), dim3(A2_NT), 0, st, p.items,
-                       p.recs, p.Yh, p.kbc, p.grid, p.partials, p.G);
+    hipLaunchKernelGGL((k_a2_spread<W, T>), dim3(p.n_items, w.slices), dim3(A2_NT), 0, st, p.items,
+                       p.recs, w.Yh, p.kbc, w.grid, w.partials, p.G, w.ray_n, w.grid_n, w.part_n);
     return hipGetLastError();
 }
 
 template <int W>
-static hipError_t launch_a2_w(const Plan& p, hipStream_t st) {
+static hipError_t launch_a2_w(const Plan& p, const Work& w, hipStream_t st) {
     switch (p.T) {
-        case 8: return launch_a2_wt<W, 8>(p, st);
-        case 16: return launch_a2_wt<W, 16>(p, st);
-        case 32: return launch_a2_wt<W, 32>(p, st);
+        case 8: return launch_a2_wt<W, 8>(p, w, st);
+        case 16: return launch_a2_wt<W, 16>(p, w, st);
+        case 32: return launch_a2_wt<W, 32>(p, w, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_a2(const Plan& p, hipStream_t st) {
+hipError_t launch_a2(const Plan& p, const Work& w, hipStream_t st) {
     switch (p.W) {
-        case 4: return launch_a2_w<4>(p, st);
-        case 6: return launch_a2_w<6>(p, st);
-        case 8: return launch_a2_w<8>(p, st);
+        case 4: return launch_a2_w<4>(p, w, st);
+        case 6: return launch_a2_w<6>(p, w, st);
+        case 8: return launch_a2_w<8>(p, w, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_a2_reduce(const Plan& p, hipStream_t st) {
-    if (p.n_splits == 0) return hipSuccess;
-    switch (p.T) {
-        case 8: hipLaunchKernelGGL((k_a2_reduce<8>), dim3(p.n_splits, (A2_GX * 8 * 8 + 255) / 256), dim3(256), 0, st, p.splits, p.partials, p.grid, p.G); break;
-        case 16: hipLaunchKernelGGL((k_a2_reduce<16>), dim3(p.n_splits, (A2_GX * 16 * 16 + 255) / 256), dim3(256), 0, st, p.splits, p.partials, p.grid, p.G); break;
-        case 32: hipLaunchKernelGGL((k_a2_reduce<32>), dim3(p.n_splits, (A2_GX * 32 * 32 + 255) / 256), dim3(256), 0, st, p.splits, p.partials, p.grid, p.G); break;
-        default: return hipErrorInvalidValue;
-    }
+template <int T>
+static hipError_t launch_a2_reduce_t(const Plan& p, const Work& w, hipStream_t st) {
+    hipLaunchKernelGGL((k_a2_reduce<T>), dim3(p.n_splits, (A2_GX * T * T + 255) / 256, w.slices), dim3(256), 0, st, p.splits,
+                       w.partials, w.grid, p.G, w.grid_n, w.part_n);
     return hipGetLastError();
 }
 
-hipError_t launch_a3(const Plan& p, hipStream_t st) {
-    const dim3 grid(p.n + 1);
+hipError_t launch_a2_reduce(const Plan& p, const Work& w, hipStream_t st) {
+    if (p.n_splits == 0) return hipSuccess;
+    switch (p.T) {
+        case 8: return launch_a2_reduce_t<8>(p, w, st);
+        case 16: return launch_a2_reduce_t<16>(p, w, st);
+        case 32: return launch_a2_reduce_t<32>(p, w, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st) {
+    const dim3 grid(p.n + 1, w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = col_threads(L);                                                   \
-        hipLaunchKernelGGL((k_a3_cols<L, NT>), grid, dim3(NT), 0, st, p.grid, p.T1, p.shift_n,  \
-                           p.tw_n);                                                            \
+        hipLaunchKernelGGL((k_a3_cols<L, NT>), grid, dim3(NT), 0, st, w.grid, w.T1, p.shift_n,  \
+                           p.tw_n, w.grid_n, w.t1_n);                                          \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)
@@ -80,14 +86,14 @@ hipError_t launch_a3(const Plan& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_a4(const Plan& p, float* img, hipStream_t st) {
-    const dim3 grid(row_blocks(p.n));
+hipError_t launch_a4(const Plan& p, const Work& w, float* img, hipStream_t st) {
+    const dim3 grid(row_blocks(p.n), w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = row_threads(L);                                                   \
-        hipLaunchKernelGGL((k_a4_rows<L, NT>), grid, dim3(NT), 0, st, p.T1, img, p.psi_inv,     \
-                           p.shift_n, p.tw_n);                                                 \
+        hipLaunchKernelGGL((k_a4_rows<L, NT>), grid, dim3(NT), 0, st, w.T1, img, p.psi_inv,     \
+                           p.shift_n, p.tw_n, w.t1_n, w.img_n);                                \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)

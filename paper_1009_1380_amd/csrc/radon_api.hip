@@ -218,31 +218,76 @@ radon_status_t launch_status(hipError_t e, const char* what) {
     return RADON_OK;
 }
 
-radon_status_t run_forward(Plan& p, const float* img, float* sino, hipStream_t st) {
+radon_status_t run_forward(Plan& p, const rn::Work& w, const float* img, float* sino, hipStream_t st) {
     radon_status_t s;
-    if ((s = launch_status(staged(p, rn::ST_F1, st, [&] { return rn::launch_f1(p, img, st); }), "F1"))) return s;
-    if ((s = launch_status(staged(p, rn::ST_F2, st, [&] { return rn::launch_f2(p, st); }), "F2"))) return s;
-    if ((s = launch_status(staged(p, rn::ST_F3, st, [&] { return rn::launch_f3(p, st); }), "F3"))) return s;
-    if ((s = launch_status(staged(p, rn::ST_F4, st, [&] { return rn::launch_f4(p, sino, st); }), "F4"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_F1, st, [&] { return rn::launch_f1(p, w, img, st); }), "F1"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_F2, st, [&] { return rn::launch_f2(p, w, st); }), "F2"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_F3, st, [&] { return rn::launch_f3(p, w, st); }), "F3"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_F4, st, [&] { return rn::launch_f4(p, w, sino, st); }), "F4"))) return s;
     return RADON_OK;
 }
 
-radon_status_t run_adjoint_grid(Plan& p, const float* sino, hipStream_t st, bool filtered = false) {
+radon_status_t run_adjoint_grid(Plan& p, const rn::Work& w, const float* sino, hipStream_t st, bool filtered = false) {
     radon_status_t s;
-    if ((s = launch_status(staged(p, rn::ST_A1, st, [&] { return rn::launch_a1(p, sino, filtered, st); }), "A1")))
+    if ((s = launch_status(staged(p, rn::ST_A1, st, [&] { return rn::launch_a1(p, w, sino, filtered, st); }), "A1")))
         return s;
-    if ((s = launch_status(staged(p, rn::ST_A2, st, [&] { return rn::launch_a2(p, st); }), "A2"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_A2, st, [&] { return rn::launch_a2(p, w, st); }), "A2"))) return s;
     if (p.n_splits > 0)
-        if ((s = launch_status(staged(p, rn::ST_A2R, st, [&] { return rn::launch_a2_reduce(p, st); }), "A2 reduce"))) return s;
+        if ((s = launch_status(staged(p, rn::ST_A2R, st, [&] { return rn::launch_a2_reduce(p, w, st); }), "A2 reduce"))) return s;
     return RADON_OK;
 }
 
-radon_status_t run_adjoint(Plan& p, const float* sino, float* img, hipStream_t st, bool filtered = false) {
+radon_status_t run_adjoint(Plan& p, const rn::Work& w, const float* sino, float* img, hipStream_t st,
+                           bool filtered = false) {
     radon_status_t s;
-    if ((s = run_adjoint_grid(p, sino, st, filtered))) return s;
-    if ((s = launch_status(staged(p, rn::ST_A3, st, [&] { return rn::launch_a3(p, st); }), "A3"))) return s;
-    if ((s = launch_status(staged(p, rn::ST_A4, st, [&] { return rn::launch_a4(p, img, st); }), "A4"))) return s;
+    if ((s = run_adjoint_grid(p, w, sino, st, filtered))) return s;
+    if ((s = launch_status(staged(p, rn::ST_A3, st, [&] { return rn::launch_a3(p, w, st); }), "A3"))) return s;
+    if ((s = launch_status(staged(p, rn::ST_A4, st, [&] { return rn::launch_a4(p, w, img, st); }), "A4"))) return s;
     return RADON_OK;
+}
+
+// Slices per pass of the batched calls, and their workspace (allocated by the
+// first call that can use it, kept with the plan, never moved, so that captured
+// graphs stay valid). A slice of up to about 1500^2 leaves CUs idle in every
+// pass; eight together, or as many as fit 128 MiB (half the last-level cache,
+// which then still holds what one pass hands to the next). 8 slices of 512^2,
+// 180 views: forward and adjoint 436 us one by one, 100 together. One at a time
+// under profiling (a
+// stage time is one slice's), or where the workspace cannot be had: no memory,
+// or the stream is being captured, which forbids the allocation.
+int stack_slices(Plan& p, int batch, hipStream_t st) {
+    if (batch < 2 || p.profiling || p.stack == 1) return 1;
+    if (p.stack == 0) {
+        const rn::Work w = rn::plan_work(p);
+        const size_t counts[5] = {w.t1_n, w.grid_n, w.ray_n, w.ray_n, w.part_n};
+        float2** bufs[5] = {&p.sT1, &p.sgrid, &p.sYh, &p.sXr, &p.spartials};
+        size_t per = 0;
+        for (size_t c : counts) per += (c * sizeof(float2) + 255) / 256 * 256;
+        const int slices = (int)std::min<size_t>(8, ((size_t)128 << 20) / per);
+        if (slices < 2) { p.stack = 1; return 1; }
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return 1;
+        }
+        void* base = nullptr;
+        size_t bytes = 0;
+        for (size_t c : counts) bytes += (c * sizeof(float2) * slices + 255) / 256 * 256;
+        if (hipMalloc(&base, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            p.stack = 1;
+            return 1;
+        }
+        p.allocs.push_back(base);
+        p.bytes += bytes;
+        char* at = static_cast<char*>(base);
+        for (int k = 0; k < 5; ++k) {
+            *bufs[k] = reinterpret_cast<float2*>(at);
+            at += (counts[k] * sizeof(float2) * slices + 255) / 256 * 256;
+        }
+        p.stack = slices;
+    }
+    return std::min(p.stack, batch);
 }
 
 // Device sort of the sample keys: keys, LSD radix passes, bin offsets.
@@ -408,7 +453,8 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
             (void)hipGetLastError();
             cus = 1;
         }
-        p.f3_grid = std::max(1, std::min(p.n_fitems, rn::f3_blocks_per_cu(p.W, p.T) * cus));
+        p.f3_resident = std::max(1, rn::f3_blocks_per_cu(p.W, p.T) * cus);
+        p.f3_grid = std::max(1, std::min(p.n_fitems, p.f3_resident));
     }
     p.n_splits = (int)splits.size();
     p.n_slots = slots;
@@ -498,14 +544,29 @@ radon_status_t build_plan(Plan& p, int n, const double* angles, int n_views, int
 }  // namespace
 
 namespace rn {
+Work plan_work(const Plan& p) {
+    const size_t n = p.n, rays = (size_t)p.n_views * (p.n_det / 2 + 1);
+    return Work{1, p.T1, p.grid, p.Yh, p.Xr, p.partials, (n + 1) * n, (n + 1) * p.G, rays,
+                (size_t)std::max(p.n_slots, 1) * A2_GX * p.T * p.T, n * n, (size_t)p.n_views * p.n_det};
+}
+Work stack_work(const Plan& p, int slices) {
+    Work w = plan_work(p);
+    w.slices = slices;
+    w.T1 = p.sT1;
+    w.grid = p.sgrid;
+    w.Yh = p.sYh;
+    w.Xr = p.sXr;
+    w.partials = p.spartials;
+    return w;
+}
 radon_status_t api_fail(radon_status_t st, const char* msg) { return fail(st, "%s", msg); }
 radon_status_t api_ok() { return ok(); }
 radon_status_t api_check_plan(radon_plan_t plan) { return check_plan(plan); }
 radon_status_t api_run_forward(Plan& p, const float* img, float* sino, hipStream_t st) {
-    return run_forward(p, img, sino, st);
+    return run_forward(p, plan_work(p), img, sino, st);
 }
 radon_status_t api_run_adjoint(Plan& p, const float* sino, float* img, hipStream_t st) {
-    return run_adjoint(p, sino, img, st);
+    return run_adjoint(p, plan_work(p), sino, img, st);
 }
 bool length_supported(int len) {
     switch (len) {
@@ -598,7 +659,7 @@ radon_status_t radon_forward(radon_plan_t plan, const float* img_dev, float* sin
     radon_status_t s;
     if ((s = check_plan(plan))) return s;
     if (!img_dev || !sino_dev) return fail(RADON_ERR_INVALID, "NULL buffer");
-    if ((s = run_forward(plan->p, img_dev, sino_dev, (hipStream_t)stream))) return s;
+    if ((s = run_forward(plan->p, rn::plan_work(plan->p), img_dev, sino_dev, (hipStream_t)stream))) return s;
     return ok();
 }
 
@@ -606,7 +667,7 @@ radon_status_t radon_adjoint(radon_plan_t plan, const float* sino_dev, float* im
     radon_status_t s;
     if ((s = check_plan(plan))) return s;
     if (!img_dev || !sino_dev) return fail(RADON_ERR_INVALID, "NULL buffer");
-    if ((s = run_adjoint(plan->p, sino_dev, img_dev, (hipStream_t)stream))) return s;
+    if ((s = run_adjoint(plan->p, rn::plan_work(plan->p), sino_dev, img_dev, (hipStream_t)stream))) return s;
     return ok();
 }
 
@@ -614,7 +675,7 @@ radon_status_t radon_fbp(radon_plan_t plan, const float* sino_dev, float* img_de
     radon_status_t s;
     if ((s = check_plan(plan))) return s;
     if (!img_dev || !sino_dev) return fail(RADON_ERR_INVALID, "NULL buffer");
-    if ((s = run_adjoint(plan->p, sino_dev, img_dev, (hipStream_t)stream, true))) return s;
+    if ((s = run_adjoint(plan->p, rn::plan_work(plan->p), sino_dev, img_dev, (hipStream_t)stream, true))) return s;
     return ok();
 }
 
@@ -624,11 +685,15 @@ radon_status_t radon_forward_batched(radon_plan_t plan, int batch, const float* 
     if ((s = check_plan(plan))) return s;
     if (batch < 0) return fail(RADON_ERR_INVALID, "batch=%d < 0", batch);
     if (batch > 0 && (!imgs_dev || !sinos_dev)) return fail(RADON_ERR_INVALID, "NULL buffer");
-    const Plan& p = plan->p;
-    for (int b = 0; b < batch; ++b)
-        if ((s = run_forward(plan->p, imgs_dev + (size_t)b * p.n * p.n,
-                             sinos_dev + (size_t)b * p.n_views * p.n_det, (hipStream_t)stream)))
+    Plan& p = plan->p;
+    hipStream_t st = (hipStream_t)stream;
+    const int per = stack_slices(p, batch, st);
+    for (int b = 0; b < batch; b += per) {
+        const int k = std::min(per, batch - b);
+        if ((s = run_forward(p, k > 1 ? rn::stack_work(p, k) : rn::plan_work(p), imgs_dev + (size_t)b * p.n * p.n,
+                             sinos_dev + (size_t)b * p.n_views * p.n_det, st)))
             return s;
+    }
     return ok();
 }
 
@@ -638,11 +703,15 @@ radon_status_t radon_adjoint_batched(radon_plan_t plan, int batch, const float* 
     if ((s = check_plan(plan))) return s;
     if (batch < 0) return fail(RADON_ERR_INVALID, "batch=%d < 0", batch);
     if (batch > 0 && (!imgs_dev || !sinos_dev)) return fail(RADON_ERR_INVALID, "NULL buffer");
-    const Plan& p = plan->p;
-    for (int b = 0; b < batch; ++b)
-        if ((s = run_adjoint(plan->p, sinos_dev + (size_t)b * p.n_views * p.n_det,
-                             imgs_dev + (size_t)b * p.n * p.n, (hipStream_t)stream)))
+    Plan& p = plan->p;
+    hipStream_t st = (hipStream_t)stream;
+    const int per = stack_slices(p, batch, st);
+    for (int b = 0; b < batch; b += per) {
+        const int k = std::min(per, batch - b);
+        if ((s = run_adjoint(p, k > 1 ? rn::stack_work(p, k) : rn::plan_work(p), sinos_dev + (size_t)b * p.n_views * p.n_det,
+                             imgs_dev + (size_t)b * p.n * p.n, st)))
             return s;
+    }
     return ok();
 }
 
@@ -755,8 +824,8 @@ radon_status_t radon_debug_forward_grid(radon_plan_t plan, const float* img_dev,
     if (!img_dev || !grid_dev) return fail(RADON_ERR_INVALID, "NULL buffer");
     Plan& p = plan->p;
     hipStream_t st = (hipStream_t)stream;
-    if ((s = launch_status(rn::launch_f1(p, img_dev, st), "F1"))) return s;
-    if ((s = launch_status(rn::launch_f2(p, st), "F2"))) return s;
+    if ((s = launch_status(rn::launch_f1(p, rn::plan_work(p), img_dev, st), "F1"))) return s;
+    if ((s = launch_status(rn::launch_f2(p, rn::plan_work(p), st), "F2"))) return s;
     if (hipMemcpyAsync(grid_dev, p.grid, sizeof(float2) * (size_t)(p.n + 1) * p.G, hipMemcpyDeviceToDevice, st) !=
         hipSuccess)
         return fail(RADON_ERR_DEVICE, "grid copy failed");
@@ -771,7 +840,7 @@ radon_status_t radon_debug_adjoint_grid(radon_plan_t plan, const float* sino_dev
     hipStream_t st = (hipStream_t)stream;
     const bool prof = p.profiling;
     p.profiling = false;
-    s = run_adjoint_grid(p, sino_dev, st);
+    s = run_adjoint_grid(p, rn::plan_work(p), sino_dev, st);
     p.profiling = prof;
     if (s) return s;
     if (hipMemcpyAsync(grid_dev, p.grid, sizeof(float2) * (size_t)(p.n + 1) * p.G, hipMemcpyDeviceToDevice, st) !=

@@ -2,18 +2,20 @@
 // F3 tiled polar interpolation, F4 ray inverse FFT), dispatched on the FFT
 // length, kernel width and tile size: for one slice, and for every slice of
 // an uneven batch (radon_multi.hpp).
+#include <algorithm>
+
 #include "radon_internal.hpp"
 
 namespace rn {
 
-hipError_t launch_f1(const Plan& p, const float* img, hipStream_t st) {
-    const dim3 grid(row_blocks(p.n));
+hipError_t launch_f1(const Plan& p, const Work& w, const float* img, hipStream_t st) {
+    const dim3 grid(row_blocks(p.n), w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = row_threads(L);                                                   \
-        hipLaunchKernelGGL((k_f1_rows<L, NT>), grid, dim3(NT), 0, st, img, p.T1, p.psi_inv,     \
-                           p.shift_n, p.tw_n);                                                 \
+        hipLaunchKernelGGL((k_f1_rows<L, NT>), grid, dim3(NT), 0, st, img, w.T1, p.psi_inv,     \
+                           p.shift_n, p.tw_n, w.img_n, w.t1_n);                                \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)
@@ -24,14 +26,14 @@ hipError_t launch_f1(const Plan& p, const float* img, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_f2(const Plan& p, hipStream_t st) {
-    const dim3 grid(p.n + 1);
+hipError_t launch_f2(const Plan& p, const Work& w, hipStream_t st) {
+    const dim3 grid(p.n + 1, w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = col_threads(L);                                                   \
-        hipLaunchKernelGGL((k_f2_cols<L, NT>), grid, dim3(NT), 0, st, p.T1, p.grid, p.shift_n,  \
-                           p.tw_n);                                                            \
+        hipLaunchKernelGGL((k_f2_cols<L, NT>), grid, dim3(NT), 0, st, w.T1, w.grid, p.shift_n,  \
+                           p.tw_n, w.t1_n, w.grid_n);                                          \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)
@@ -43,10 +45,11 @@ hipError_t launch_f2(const Plan& p, hipStream_t st) {
 }
 
 template <int W, int T>
-static hipError_t launch_f3_wt(const Plan& p, hipStream_t st) {
+static hipError_t launch_f3_wt(const Plan& p, const Work& w, hipStream_t st) {
     if (p.n_fitems == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_f3_tiles<W, T, 512>), dim3(p.f3_grid), dim3(512), 0, st, p.fitems, p.n_fitems,
-                       p.recs, p.grid, p.kbc, p.Xr, p.G);
+    const int grid = w.slices == 1 ? p.f3_grid : (int)std::min<int64_t>((int64_t)p.n_fitems * w.slices, p.f3_resident);
+    hipLaunchKernelGGL((k_f3_tiles<W, T, 512>), dim3(grid), dim3(512), 0, st, p.fitems, p.n_fitems,
+                       p.recs, w.grid, p.kbc, w.Xr, p.G, w.slices, w.grid_n, w.ray_n);
     return hipGetLastError();
 }
 
@@ -80,32 +83,32 @@ int f3_blocks_per_cu(int W, int T) {
 }
 
 template <int W>
-static hipError_t launch_f3_w(const Plan& p, hipStream_t st) {
+static hipError_t launch_f3_w(const Plan& p, const Work& w, hipStream_t st) {
     switch (p.T) {
-        case 8: return launch_f3_wt<W, 8>(p, st);
-        case 16: return launch_f3_wt<W, 16>(p, st);
-        case 32: return launch_f3_wt<W, 32>(p, st);
+        case 8: return launch_f3_wt<W, 8>(p, w, st);
+        case 16: return launch_f3_wt<W, 16>(p, w, st);
+        case 32: return launch_f3_wt<W, 32>(p, w, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_f3(const Plan& p, hipStream_t st) {
+hipError_t launch_f3(const Plan& p, const Work& w, hipStream_t st) {
     switch (p.W) {
-        case 4: return launch_f3_w<4>(p, st);
-        case 6: return launch_f3_w<6>(p, st);
-        case 8: return launch_f3_w<8>(p, st);
+        case 4: return launch_f3_w<4>(p, w, st);
+        case 6: return launch_f3_w<6>(p, w, st);
+        case 8: return launch_f3_w<8>(p, w, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_f4(const Plan& p, float* sino, hipStream_t st) {
-    const dim3 grid((p.n_views + 1) / 2);
+hipError_t launch_f4(const Plan& p, const Work& w, float* sino, hipStream_t st) {
+    const dim3 grid((p.n_views + 1) / 2, w.slices);
     switch (p.n_det) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = ray_threads(L);                                                     \
-        hipLaunchKernelGGL((k_f4_rays<L, NT>), grid, dim3(NT), 0, st, p.Xr, sino, p.tw_N,       \
-                           p.n_views);                                                         \
+        hipLaunchKernelGGL((k_f4_rays<L, NT>), grid, dim3(NT), 0, st, w.Xr, sino, p.tw_N,       \
+                           p.n_views, w.ray_n, w.sino_n);                                      \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)

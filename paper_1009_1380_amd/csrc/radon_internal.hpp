@@ -46,6 +46,7 @@ struct Plan {
     int n_items = 0, n_slots = 0, n_splits = 0;   // spreading work
     int n_fitems = 0;                   // forward interpolation work
     int f3_grid = 0;                    // workgroups of the persistent forward interpolation
+    int f3_resident = 0;                // forward interpolation workgroups that fit on the device
     int a2_chunk = 0, f3_chunk = 0;     // most visits / samples per work item
 
     // device tables
@@ -69,6 +70,10 @@ struct Plan {
     TileItem* items = nullptr;
     SplitTile* splits = nullptr;
     float2* partials = nullptr;
+    // workspace of several slices at a time (radon_forward_batched and
+    // radon_adjoint_batched), allocated by the first call that uses it
+    int stack = 0;                      // slices it holds, 0 before that call, 1: not used
+    float2 *sT1 = nullptr, *sgrid = nullptr, *sYh = nullptr, *sXr = nullptr, *spartials = nullptr;
     // host copies of the work lists (batches concatenate them across slices)
     std::vector<TileItem> items_h;
     std::vector<F3Item> fitems_h;
@@ -85,17 +90,27 @@ struct Plan {
     std::vector<hipEvent_t> event_pool;
 };
 
+// The workspace of a pass over `slices` slices back to back, and the distance
+// of consecutive slices in each buffer.
+struct Work {
+    int slices;
+    float2 *T1, *grid, *Yh, *Xr, *partials;
+    size_t t1_n, grid_n, ray_n, part_n, img_n, sino_n;
+};
+Work plan_work(const Plan& p);                 // the plan's own, one slice
+Work stack_work(const Plan& p, int slices);    // the stack's
+
 // kernel launchers of one plan; each returns the launch status
-hipError_t launch_f1(const Plan& p, const float* img, hipStream_t st);
-hipError_t launch_f2(const Plan& p, hipStream_t st);
-hipError_t launch_f3(const Plan& p, hipStream_t st);
+hipError_t launch_f1(const Plan& p, const Work& w, const float* img, hipStream_t st);
+hipError_t launch_f2(const Plan& p, const Work& w, hipStream_t st);
+hipError_t launch_f3(const Plan& p, const Work& w, hipStream_t st);
 int f3_blocks_per_cu(int W, int T);   // resident forward-interpolation workgroups per CU
-hipError_t launch_f4(const Plan& p, float* sino, hipStream_t st);
-hipError_t launch_a1(const Plan& p, const float* sino, bool filtered, hipStream_t st);
-hipError_t launch_a2(const Plan& p, hipStream_t st);
-hipError_t launch_a2_reduce(const Plan& p, hipStream_t st);
-hipError_t launch_a3(const Plan& p, hipStream_t st);
-hipError_t launch_a4(const Plan& p, float* img, hipStream_t st);
+hipError_t launch_f4(const Plan& p, const Work& w, float* sino, hipStream_t st);
+hipError_t launch_a1(const Plan& p, const Work& w, const float* sino, bool filtered, hipStream_t st);
+hipError_t launch_a2(const Plan& p, const Work& w, hipStream_t st);
+hipError_t launch_a2_reduce(const Plan& p, const Work& w, hipStream_t st);
+hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st);
+hipError_t launch_a4(const Plan& p, const Work& w, float* img, hipStream_t st);
 // Launchers for uneven batches (radon_multi.hpp): one transform pass over the
 // slices of a device table, and the gridding pass of one (W, T) group.
 enum PassKind { PK_F1, PK_F2, PK_F4, PK_A1, PK_A3, PK_A4 };

@@ -1103,81 +1103,88 @@ __device__ __forceinline__ void a4_body(int bid_, int nblk_, const float2* __res
     }
 }
 
-// ---------------------------------------------------------------- single-slice kernels
-// One launch per pass of one slice (batches use radon_multi.hpp's kernels,
-// which run the same bodies).
+// ---------------------------------------------------------------- one plan's kernels
+// One launch per pass of one slice, or of several slices that share a plan:
+// blockIdx.y (z for the split-strip sums) is the slice, whose buffers lie `is`
+// and `os` elements after the previous slice's (batches of uneven slices use
+// radon_multi.hpp's kernels, which run the same bodies).
 template <int NL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_f1_rows(
     const float* __restrict__ img, float2* __restrict__ T1, const float* __restrict__ psi_inv,
-    const float2* __restrict__ shift, const float2* __restrict__ tw) {
-    f1_body<NL, NT>(blockIdx.x, gridDim.x, img, T1, psi_inv, shift, tw);
+    const float2* __restrict__ shift, const float2* __restrict__ tw, size_t is, size_t os) {
+    f1_body<NL, NT>(blockIdx.x, gridDim.x, img + blockIdx.y * is, T1 + blockIdx.y * os, psi_inv, shift, tw);
 }
 
 template <int NL, int NT>
 __global__ __launch_bounds__(NT) void k_f2_cols(const float2* __restrict__ T1, float2* __restrict__ grid,
-                                               const float2* __restrict__ shift, const float2* __restrict__ tw) {
-    f2_body<NL, NT>(blockIdx.x, gridDim.x, T1, grid, shift, tw);
+                                               const float2* __restrict__ shift, const float2* __restrict__ tw,
+                                               size_t is, size_t os) {
+    f2_body<NL, NT>(blockIdx.x, gridDim.x, T1 + blockIdx.y * is, grid + blockIdx.y * os, shift, tw);
 }
 
 // Persistent: workgroup b takes items b, b + gridDim.x, ... (the grid is the
-// number of workgroups that fit on the device at once).
+// number of workgroups that fit on the device at once). Consecutive workgroups
+// take the same item of consecutive slices, which share its records.
 template <int W, int T, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(W <= 6 ? RN_F3_WPE : 1))) void k_f3_tiles(
     const F3Item* __restrict__ items, int n_items, const SampleRec* __restrict__ recs,
-    const float2* __restrict__ grid, const float4* __restrict__ kbc, float2* __restrict__ Xr, int G) {
+    const float2* __restrict__ grid, const float4* __restrict__ kbc, float2* __restrict__ Xr, int G, int slices,
+    size_t is, size_t os) {
     constexpr int PP = (2 * T + W - 1) * (2 * T + W - 1);
     constexpr int NKB = (W / 2) * KB_S;
     __shared__ float2 tile[PP];   // [lx][ly], lx along u (mx), ly along v (my)
     __shared__ float4 kbt[NKB];
     const int tid = threadIdx.x;
     for (int e = tid; e < NKB; e += NT) kbt[e] = kbc[e];
-    for (int i = blockIdx.x; i < n_items; i += gridDim.x) {
-        const F3Item it = items[i];
-        f3_item<W, T, NT>(it, recs, grid, Xr, G, tile, kbt, tid);
+    for (int i = blockIdx.x; i < n_items * slices; i += gridDim.x) {
+        const int e = slices == 1 ? i : i / slices, b = i - e * slices;
+        const F3Item it = items[e];
+        f3_item<W, T, NT>(it, recs, grid + b * is, Xr + b * os, G, tile, kbt, tid);
     }
 }
 
 template <int ND, int NT>
 __global__ __launch_bounds__(NT) void k_f4_rays(const float2* __restrict__ Xr, float* __restrict__ sino,
-                                               const float2* __restrict__ tw, int n_views) {
-    f4_body<ND, NT>(blockIdx.x, gridDim.x, Xr, sino, tw, n_views);
+                                               const float2* __restrict__ tw, int n_views, size_t is, size_t os) {
+    f4_body<ND, NT>(blockIdx.x, gridDim.x, Xr + blockIdx.y * is, sino + blockIdx.y * os, tw, n_views);
 }
 
 template <int ND, int NT>
 __global__ __launch_bounds__(NT) void k_a1_rays(const float* __restrict__ sino, float2* __restrict__ Yh,
                                                const float2* __restrict__ tw, const float* __restrict__ wq,
-                                               int n_views) {
-    a1_body<ND, NT>(blockIdx.x, gridDim.x, sino, Yh, tw, wq, n_views);
+                                               int n_views, size_t is, size_t os) {
+    a1_body<ND, NT>(blockIdx.x, gridDim.x, sino + blockIdx.y * is, Yh + blockIdx.y * os, tw, wq, n_views);
 }
 
 template <int W, int T>
 __global__ __launch_bounds__(A2_NT) __attribute__((amdgpu_waves_per_eu(W <= 6 ? RN_A2_WPE : 1))) void k_a2_spread(
     const TileItem* __restrict__ items, const SampleRec* __restrict__ recs,
     const float2* __restrict__ Yh, const float4* __restrict__ kbc, float2* __restrict__ grid,
-    float2* __restrict__ partials, int G) {
+    float2* __restrict__ partials, int G, size_t is, size_t os, size_t ps) {
     const TileItem it = items[blockIdx.x];
-    a2_item<W, T>(it, recs, Yh, kbc, grid, partials, G);
+    a2_item<W, T>(it, recs, Yh + blockIdx.y * is, kbc, grid + blockIdx.y * os, partials + blockIdx.y * ps, G);
 }
 
 template <int T>
 __global__ __launch_bounds__(256) void k_a2_reduce(const SplitTile* __restrict__ splits,
                                                   const float2* __restrict__ partials, float2* __restrict__ grid,
-                                                  int G) {
+                                                  int G, size_t os, size_t ps) {
     const SplitTile sp = splits[blockIdx.x];
-    a2r_body<T>(sp, blockIdx.y, partials, grid, G);
+    a2r_body<T>(sp, blockIdx.y, partials + blockIdx.z * ps, grid + blockIdx.z * os, G);
 }
 
 template <int NL, int NT>
 __global__ __launch_bounds__(NT) void k_a3_cols(const float2* __restrict__ grid, float2* __restrict__ T1,
-                                               const float2* __restrict__ shift, const float2* __restrict__ tw) {
-    a3_body<NL, NT>(blockIdx.x, gridDim.x, grid, T1, shift, tw);
+                                               const float2* __restrict__ shift, const float2* __restrict__ tw,
+                                               size_t is, size_t os) {
+    a3_body<NL, NT>(blockIdx.x, gridDim.x, grid + blockIdx.y * is, T1 + blockIdx.y * os, shift, tw);
 }
 
 template <int NL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_a4_rows(
     const float2* __restrict__ T1, float* __restrict__ img, const float* __restrict__ psi_inv,
-    const float2* __restrict__ shift, const float2* __restrict__ tw) {
-    a4_body<NL, NT>(blockIdx.x, gridDim.x, T1, img, psi_inv, shift, tw);
+    const float2* __restrict__ shift, const float2* __restrict__ tw, size_t is, size_t os) {
+    a4_body<NL, NT>(blockIdx.x, gridDim.x, T1 + blockIdx.y * is, img + blockIdx.y * os, psi_inv, shift, tw);
 }
 
 // ---------------------------------------------------------------- FFT test
