@@ -549,6 +549,66 @@ __device__ __forceinline__ void f3_item(const F3Item& it, const SampleRec* __res
     }
 }
 
+// The same interpolation without staging: one thread per sorted sample reads its
+// W x W points from the grid (the samples of a wave, neighbours in the sort,
+// share most cache lines). Bound by the addresses it generates, so it pays where
+// the samples are few (f3_is_direct). The points, weights and order of the sums are those
+// of f3_item, so the results are the same bit for bit. `e`: sample position.
+template <int W>
+__device__ __forceinline__ void f3_direct(int e, int n_samples, const SampleRec* __restrict__ recs,
+                                          const float2* __restrict__ grid, float2* __restrict__ Xr, int G, int T,
+                                          const float4* __restrict__ kbc, float4* kbt, int tid, int nt) {
+    constexpr int NKB = (W / 2) * KB_S;
+    SampleRec r{};
+    if (e < n_samples) r = load_rec(recs, e);
+    for (int k = tid; k < NKB; k += nt) kbt[k] = kbc[k];
+    lds_sync();
+    // one member of each conjugate pair: flagged, and with its origin in a forward column
+    if (!((unsigned)r.info & REC_F3) || !forward_column((r.org & REC_ORG_MASK) / T, G / T)) return;
+    const int ox = (r.org & REC_ORG_MASK) - G / 2, oy = ((r.org >> 16) & REC_ORG_MASK) - G / 2;   // in [-G/2, G/2)
+    int cy[W], cm[W];   // grid columns my mod G of the footprint, and of its mirror image
+#pragma unroll
+    for (int gm = 0; gm < W; ++gm) {
+        cy[gm] = wrap_g(oy + gm, G);
+        cm[gm] = cy[gm] == 0 ? 0 : G - cy[gm];
+    }
+    float2 v[W][W];
+#pragma unroll
+    for (int al = 0; al < W; ++al) {
+        int mx = ox + al;                       // at most G/2 + W - 2: past G/2 it is a negative frequency
+        if (mx > G / 2) mx -= G;
+        if (mx == -G / 2) mx = G / 2;
+        const bool mirror = mx < 0;
+        const float2* row = grid + (size_t)(mirror ? -mx : mx) * G;
+#pragma unroll
+        for (int gm = 0; gm < W; ++gm) {
+            v[al][gm] = row[mirror ? cm[gm] : cy[gm]];
+            if (mirror) v[al][gm].y = -v[al][gm].y;
+        }
+    }
+    float wy[W], wx[W];
+    kb_weights<W>(r.fv, kbt, wy);
+    if (r.org & REC_V_NEAR_OUT) wy[0] = 0.f;
+    if (r.org & REC_V_FAR_OUT) wy[W - 1] = 0.f;
+    kb_weights<W>(r.fu, kbt, wx);
+    if (r.org & REC_U_NEAR_OUT) wx[0] = 0.f;
+    if (r.org & REC_U_FAR_OUT) wx[W - 1] = 0.f;
+    float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int al = 0; al < W; ++al) {
+        float2 racc = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int gm = 0; gm < W; ++gm) {
+            racc.x = fmaf(wy[gm], v[al][gm].x, racc.x);
+            racc.y = fmaf(wy[gm], v[al][gm].y, racc.y);
+        }
+        acc.x = fmaf(wx[al], racc.x, acc.x);
+        acc.y = fmaf(wx[al], racc.y, acc.y);
+    }
+    const bool cj = (r.info & (REC_CONJ | REC_MIRROR)) != 0;
+    Xr[r.info & REC_IDX_MASK] = cj ? cconj(acc) : acc;
+}
+
 // ---------------------------------------------------------------- F4
 // Two rays per workgroup: y = Re((1/N) IFFT) of the Hermitian extension
 // X[-q] = conj X[q] of Xr (bins 0 and N/2 taken as real); the two real
@@ -1141,6 +1201,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(W <= 6 ? RN_
         const F3Item it = items[e];
         f3_item<W, T, NT>(it, recs, grid + b * is, Xr + b * os, G, tile, kbt, tid);
     }
+}
+
+constexpr int F3D_NT = 256;
+template <int W>
+__global__ __launch_bounds__(F3D_NT) void k_f3_direct(const SampleRec* __restrict__ recs, int n_samples,
+                                                     const float2* __restrict__ grid, const float4* __restrict__ kbc,
+                                                     float2* __restrict__ Xr, int G, int T, size_t is, size_t os) {
+    __shared__ float4 kbt[(W / 2) * KB_S];
+    f3_direct<W>(blockIdx.x * F3D_NT + threadIdx.x, n_samples, recs, grid + blockIdx.y * is, Xr + blockIdx.y * os, G, T, kbc,
+                 kbt, threadIdx.x, F3D_NT);
 }
 
 template <int ND, int NT>
