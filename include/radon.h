@@ -264,8 +264,8 @@ radon_status_t radon_ring_filter(radon_plan_t plan, const float* y_dev, float* o
  * HIP stream capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same operation and result as radon_ring_filter, with no allocation of
  * any kind. The cubic basis is the plan's own; the scratch of its three
- * kernels (column means, fitted ring, partial sums) is one file-scope device
- * array of 2 * RADON_RING_NOALLOC_MAX_DET + 4096 float64 values (96 KiB),
+ * kernels (column sums, fitted ring, partial sums) is one file-scope device
+ * array of 9 * RADON_RING_NOALLOC_MAX_DET + 4096 float64 values (320 KiB),
  * of which every GPU the library runs on holds its own copy until the
  * process ends. Every call on a GPU shares that GPU's array: calls that
  * overlap on one GPU (several streams, several threads) race and must be

@@ -15,6 +15,7 @@
 // sums the partials in block order), so a solve is bitwise reproducible.
 // The host loop reads back a handful of float64 scalars per iteration.
 #include <math.h>
+#include <stdint.h>
 
 #include <algorithm>
 #include <chrono>
@@ -98,19 +99,39 @@ __global__ __launch_bounds__(SV_NT) void k_sv_final(const double* __restrict__ p
     }
 }
 
-// m[d] = mean over views of (b - z)[., d] (z may be null: m = mean of b).
-// A block takes 32 detectors; its 8 thread groups sum every 8th view, and the
-// 8 group sums are added in group order.
-__global__ __launch_bounds__(256) void k_sv_colmean(const float* __restrict__ b, const float* __restrict__ z,
-                                                   int nv, int N, double* __restrict__ m) {
+// msum[c][d] = sum over the views of chunk c of (b - z)[., d] (z may be null).
+// A block takes 32 detectors and one of at most CM_CHUNKS chunks of views; its 8
+// thread groups sum every 8th view of the chunk, four views' loads in flight, and
+// the 8 group sums are added in group order. Bound by latency, so the chunks,
+// which put more workgroups on the chip, are what helps: all views in one chunk
+// took 7.9 us at 128 views x 1024 detectors and 22 at 1024 x 2560, in chunks 4.3
+// and 8.7; 16 loads in flight in one chunk took 10.6 and 9.8.
+constexpr int CM_CHUNKS = 8;       // most chunks
+constexpr int CM_VIEWS = 32;       // views that fill a chunk (8 groups of 4)
+__host__ __device__ inline int colsum_chunks(int nv) {
+    const int c = (nv + CM_VIEWS - 1) / CM_VIEWS;
+    return c < CM_CHUNKS ? c : CM_CHUNKS;
+}
+__global__ __launch_bounds__(256) void k_sv_colsum(const float* __restrict__ b, const float* __restrict__ z,
+                                                  int nv, int N, double* __restrict__ msum) {
+    constexpr int U = 4;
     __shared__ double part[8][32];
     const int dl = threadIdx.x & 31, g = threadIdx.x >> 5;
     const int d = blockIdx.x * 32 + dl;
+    const int per = (nv + gridDim.y - 1) / gridDim.y, a0 = blockIdx.y * per, a1 = min(nv, a0 + per);
     double s = 0.0;
     if (d < N) {
-        for (int a = g; a < nv; a += 8) {
-            const size_t i = (size_t)a * N + d;
-            s += (double)b[i] - (z ? (double)z[i] : 0.0);
+        for (int a = a0 + g; a < a1; a += 8 * U) {
+            float bv[U], zv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const size_t i = (size_t)(a + 8 * u) * N + d;
+                const bool in = a + 8 * u < a1;
+                bv[u] = in ? b[i] : 0.f;
+                zv[u] = in && z ? z[i] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += (double)bv[u] - (double)zv[u];
         }
     }
     part[g][dl] = s;
@@ -118,24 +139,42 @@ __global__ __launch_bounds__(256) void k_sv_colmean(const float* __restrict__ b,
     if (g == 0 && d < N) {
         double t = part[0][dl];
         for (int k = 1; k < 8; ++k) t += part[k][dl];
-        m[d] = t / nv;
+        msum[(size_t)blockIdx.y * N + d] = t;
     }
 }
 
-// ring[d] = m[d] - (Q Q^T m)[d]  (one block). The four coefficients
-// c_k = sum_d Q[d][k] m[d] are accumulated together, each in the order of
-// block_reduce (per thread over d, then the waves, then the wave sums in order).
-__global__ __launch_bounds__(SV_NT) void k_sv_ringfit(const double* __restrict__ m, const double* __restrict__ Q,
-                                                     int N, double* __restrict__ ring) {
-    __shared__ double sh[4][SV_NT / 64];
+// ring[d] = m[d] - (Q Q^T m)[d] (one block), m the column means from the sums of
+// `chunks` chunks. The four coefficients c_k = sum_d Q[d][k] m[d] are
+// accumulated together (per thread over d, then the waves, then the wave sums in
+// order). N <= 4 RF_NT.
+constexpr int RF_NT = 1024;
+__global__ __launch_bounds__(RF_NT) void k_sv_ringfit(const double* __restrict__ msum, int chunks, int nv,
+                                                     const double* __restrict__ Q, int N, double* __restrict__ ring) {
+    __shared__ double sh[4][RF_NT / 64];
     __shared__ double c[4];
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int d = threadIdx.x; d < N; d += SV_NT) {
-        const double md = m[d];
-        const double* q = Q + (size_t)d * 4;
+    constexpr int PER = 4;
+    double m[PER], q[PER][4], v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] += q[k] * md;
+    for (int j = 0; j < PER; ++j) {
+        const int d = threadIdx.x + j * RF_NT;
+        m[j] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[j][k] = 0.0;
+        if (d < N) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[j][k] = Q[(size_t)d * 4 + k];
+            double p[CM_CHUNKS];
+#pragma unroll
+            for (int k = 0; k < CM_CHUNKS; ++k) p[k] = k < chunks ? msum[(size_t)k * N + d] : 0.0;
+#pragma unroll
+            for (int k = 0; k < CM_CHUNKS; ++k) m[j] += p[k];
+            m[j] /= nv;
+        }
     }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += q[j][k] * m[j];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -146,36 +185,79 @@ __global__ __launch_bounds__(SV_NT) void k_sv_ringfit(const double* __restrict__
     if (threadIdx.x < 4) {
         const int k = threadIdx.x;
         double r = sh[k][0];
-        for (int w = 1; w < SV_NT / 64; ++w) r += sh[k][w];
+        for (int w = 1; w < RF_NT / 64; ++w) r += sh[k][w];
         c[k] = r;
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < N; d += SV_NT) {
-        const double* q = Q + (size_t)d * 4;
-        ring[d] = m[d] - (q[0] * c[0] + q[1] * c[1] + q[2] * c[2] + q[3] * c[3]);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int d = threadIdx.x + j * RF_NT;
+        if (d < N) ring[d] = m[j] - (q[j][0] * c[0] + q[j][1] * c[1] + q[j][2] * c[2] + q[j][3] * c[3]);
     }
 }
 
 // r = (b - z) - ring[d] (ring may be null; z may be null); partials of
-// slot 0: sum r^2, slot 1: sum r * bt (bt may be null).
-__global__ __launch_bounds__(SV_NT) void k_sv_resid(const float* __restrict__ b, const float* __restrict__ z,
+// slot 0: sum r^2, slot 1: sum r * bt (bt may be null). r may be b. A block takes
+// a contiguous run of pieces of V detectors (V = 4 where all the arrays are
+// 16-byte aligned, else 1; N is a multiple of 4), whose detector it steps without
+// a division per element.
+template <int V>
+__global__ __launch_bounds__(SV_NT) void k_sv_resid(const float* b, const float* __restrict__ z,
                                                    const double* __restrict__ ring, const float* __restrict__ bt,
-                                                   int nv, int N, float* __restrict__ r, double* __restrict__ part) {
+                                                   int nv, int N, float* r, double* __restrict__ part) {
     __shared__ double sh[SV_NT / 64];
-    const size_t total = (size_t)nv * N;
+    const unsigned P = (unsigned)(N / V);                     // pieces of a row
+    const size_t total = (size_t)nv * P, per = (total + gridDim.x - 1) / gridDim.x;
+    const size_t i0 = blockIdx.x * per + threadIdx.x, i1 = min(total, (blockIdx.x + 1) * per);
+    unsigned col = (unsigned)(i0 % P);
+    const unsigned step = SV_NT % P;
     double s0 = 0.0, s1 = 0.0;
-    for (size_t i = (size_t)blockIdx.x * SV_NT + threadIdx.x; i < total; i += (size_t)gridDim.x * SV_NT) {
-        double v = (double)b[i] - (z ? (double)z[i] : 0.0);
-        if (ring) v -= ring[i % N];
-        const float rf = (float)v;
-        r[i] = rf;
-        s0 += (double)rf * rf;
-        if (bt) s1 += (double)rf * bt[i];
+    auto ld = [](const float* p, size_t i, float (&v)[V]) {
+        if constexpr (V == 4) {
+            const float4 q = reinterpret_cast<const float4*>(p)[i];
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else {
+            v[0] = p[i];
+        }
+    };
+#pragma unroll 4
+    for (size_t i = i0; i < i1; i += SV_NT) {
+        float bv[V], zv[V] = {}, tv[V] = {}, o[V];
+        ld(b, i, bv);
+        if (z) ld(z, i, zv);
+        if (bt) ld(bt, i, tv);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            double v = (double)bv[k] - (double)zv[k];
+            if (ring) v -= ring[col * V + k];
+            o[k] = (float)v;
+            s0 += (double)o[k] * o[k];
+            s1 += (double)o[k] * tv[k];
+        }
+        if constexpr (V == 4) reinterpret_cast<float4*>(r)[i] = make_float4(o[0], o[1], o[2], o[3]);
+        else r[i] = o[0];
+        col += step;
+        if (col >= P) col -= P;
     }
     double t = block_reduce<false>(s0, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = t;
     t = block_reduce<false>(s1, sh);
     if (threadIdx.x == 0) part[gridDim.x + blockIdx.x] = t;
+}
+
+// r = F(b - z), or b - z without a basis Q; msum: CM_CHUNKS x N, ring: N. Enqueues
+// only.
+void launch_residual(const float* b, const float* z, const double* Q, const float* bt, int nv, int N, double* msum,
+                     double* ring, float* r, double* part, hipStream_t st) {
+    if (Q) {
+        const int chunks = colsum_chunks(nv);
+        hipLaunchKernelGGL(k_sv_colsum, dim3((N + 31) / 32, chunks), dim3(256), 0, st, b, z, nv, N, msum);
+        hipLaunchKernelGGL(k_sv_ringfit, dim3(1), dim3(RF_NT), 0, st, msum, chunks, nv, Q, N, ring);
+    }
+    const bool wide = (((uintptr_t)b | (uintptr_t)z | (uintptr_t)bt | (uintptr_t)r) & 15) == 0 && N % 4 == 0;
+    const double* rg = Q ? ring : nullptr;
+    if (wide) hipLaunchKernelGGL(k_sv_resid<4>, dim3(SV_BLOCKS), dim3(SV_NT), 0, st, b, z, rg, bt, nv, N, r, part);
+    else hipLaunchKernelGGL(k_sv_resid<1>, dim3(SV_BLOCKS), dim3(SV_NT), 0, st, b, z, rg, bt, nv, N, r, part);
 }
 
 // Barzilai-Borwein quantities with s = xn - x and y = gn - g = -(hn - h):
@@ -710,15 +792,7 @@ struct Solver {
 
     // r = F(b - z) (z may be null) -> fin[0] = sum r^2, fin[1] = sum r.bt (bt may be null)
     void residual(const float* z, float* r, const float* bt) {
-        const double* ring = nullptr;
-        if (filt) {
-            hipLaunchKernelGGL(rn::k_sv_colmean, dim3((p.n_det + 31) / 32), dim3(256), 0, st, b, z, p.n_views,
-                               p.n_det, w.m);
-            hipLaunchKernelGGL(rn::k_sv_ringfit, dim3(1), dim3(rn::SV_NT), 0, st, w.m, w.Q, p.n_det, w.ring);
-            ring = w.ring;
-        }
-        hipLaunchKernelGGL(rn::k_sv_resid, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, b, z, ring, bt, p.n_views,
-                           p.n_det, r, part(FIN_RES));
+        rn::launch_residual(b, z, filt ? w.Q : nullptr, bt, p.n_views, p.n_det, w.m, w.ring, r, part(FIN_RES), st);
         chk(hipGetLastError());
     }
 
@@ -782,18 +856,14 @@ extern "C" radon_status_t radon_ring_filter(radon_plan_t plan, const float* y_de
     if (!plan || !y_dev || !out_dev) return RADON_ERR_INVALID;
     const rn::Plan& p = plan->p;
     SolveWork w;
-    if (!w.alloc(&w.m, p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
+    if (!w.alloc(&w.m, (size_t)rn::CM_CHUNKS * p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
         !w.alloc(&w.part, (size_t)rn::SV_SLOTS * rn::SV_BLOCKS))
         return RADON_ERR_OOM;
     hipStream_t st = (hipStream_t)stream;
     const std::vector<double> Q = cubic_basis(p.n_det);
     if (hipMemcpy(w.Q, Q.data(), sizeof(double) * Q.size(), hipMemcpyHostToDevice) != hipSuccess)
         return RADON_ERR_DEVICE;
-    hipLaunchKernelGGL(rn::k_sv_colmean, dim3((p.n_det + 31) / 32), dim3(256), 0, st, y_dev, nullptr, p.n_views,
-                       p.n_det, w.m);
-    hipLaunchKernelGGL(rn::k_sv_ringfit, dim3(1), dim3(rn::SV_NT), 0, st, w.m, w.Q, p.n_det, w.ring);
-    hipLaunchKernelGGL(rn::k_sv_resid, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, y_dev, nullptr, w.ring, nullptr,
-                       p.n_views, p.n_det, out_dev, w.part);
+    rn::launch_residual(y_dev, nullptr, w.Q, nullptr, p.n_views, p.n_det, w.m, w.ring, out_dev, w.part, st);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return RADON_ERR_DEVICE;
     return RADON_OK;
 }
@@ -850,7 +920,7 @@ extern "C" radon_status_t radon_project_l1(const float* v_dev, int64_t n, double
 // radon_ring_filter_noalloc: the ring filter for callers that cannot allocate
 // device memory (code under stream capture, serving loops, harnesses that
 // forbid it). The cubic basis is the plan's (uploaded when the plan is made);
-// the scratch the three kernels need (column means, fitted ring, the
+// the scratch the three kernels need (column sums, fitted ring, the
 // per-block partials the residual kernel writes) lives in one file-scope
 // device array, of which every GPU holds its own copy until the process ends.
 // Every kernel overwrites the part of the array it reads back, so nothing
@@ -860,8 +930,9 @@ extern "C" radon_status_t radon_project_l1(const float* v_dev, int64_t n, double
 namespace {
 
 constexpr int RING_NOALLOC_MAX_DET = RADON_RING_NOALLOC_MAX_DET;
-// doubles: m[N], ring[N], partials[SV_SLOTS * SV_BLOCKS]
-constexpr size_t RING_SCRATCH_DOUBLES = (size_t)2 * RING_NOALLOC_MAX_DET + (size_t)rn::SV_SLOTS * rn::SV_BLOCKS;
+// doubles: column sums[CM_CHUNKS * N], ring[N], partials[SV_SLOTS * SV_BLOCKS]
+constexpr size_t RING_SCRATCH_DOUBLES =
+    (size_t)(rn::CM_CHUNKS + 1) * RING_NOALLOC_MAX_DET + (size_t)rn::SV_SLOTS * rn::SV_BLOCKS;
 
 }  // namespace
 
@@ -905,14 +976,10 @@ extern "C" radon_status_t radon_ring_filter_noalloc(radon_plan_t plan, const flo
     if (!base)
         return rn::api_fail(RADON_ERR_DEVICE, "radon_ring_filter_noalloc: no device address for the scratch array");
     double* m = base;
-    double* ring = m + RING_NOALLOC_MAX_DET;
+    double* ring = m + (size_t)rn::CM_CHUNKS * RING_NOALLOC_MAX_DET;
     double* part = ring + RING_NOALLOC_MAX_DET;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(rn::k_sv_colmean, dim3((p.n_det + 31) / 32), dim3(256), 0, st, y_dev, nullptr, p.n_views,
-                       p.n_det, m);
-    hipLaunchKernelGGL(rn::k_sv_ringfit, dim3(1), dim3(rn::SV_NT), 0, st, m, p.ringQ, p.n_det, ring);
-    hipLaunchKernelGGL(rn::k_sv_resid, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, y_dev, nullptr, ring, nullptr,
-                       p.n_views, p.n_det, out_dev, part);
+    rn::launch_residual(y_dev, nullptr, p.ringQ, nullptr, p.n_views, p.n_det, m, ring, out_dev, part, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return rn::api_fail(RADON_ERR_DEVICE, "radon_ring_filter_noalloc: launch failed");
     return rn::api_ok();
@@ -1070,7 +1137,7 @@ extern "C" radon_status_t radon_solve_bpdn(radon_plan_t plan, const float* b_dev
     const size_t n2 = (size_t)p.n * p.n, ns = (size_t)p.n_views * p.n_det;
     if (!w.alloc(&w.x, n2) || !w.alloc(&w.xn, n2) || !w.alloc(&w.h, n2) || !w.alloc(&w.hn, n2) ||
         !w.alloc(&w.z, ns) || !w.alloc(&w.r, ns) || !w.alloc(&w.rn, ns) || !w.alloc(&w.bt, ns) ||
-        !w.alloc(&w.m, p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
+        !w.alloc(&w.m, (size_t)rn::CM_CHUNKS * p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
         !w.alloc(&w.part, (size_t)FIN_COUNT * rn::SV_BLOCKS) || !w.alloc(&w.ct, 2) ||
         !w.alloc(&w.pjc, SolveWork::PJ_ALL) || !w.alloc(&w.pjs, SolveWork::PJ_ALL) || !w.alloc(&w.pjbad, 1) ||
         !w.alloc(&w.pjst, 2) || !w.alloc_host(&w.fin_h, FIN_COUNT))
