@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <chrono>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "../../include/radon.h"
@@ -705,10 +706,12 @@ std::vector<double> ring_cubic_basis(int N) {
 namespace {
 
 struct SolveWork {
-    std::vector<void*> allocs, host_allocs;
+    void* arena = nullptr;                           // the call's device memory, one allocation
+    std::vector<std::pair<void**, size_t>> wanted;   // what it holds: pointer, offset
+    size_t bytes = 0, cleared = 0;                   // its size; the first `cleared` bytes start at zero
     float *x = nullptr, *xn = nullptr, *h = nullptr, *hn = nullptr;
     float *z = nullptr, *r = nullptr, *rn = nullptr, *bt = nullptr;
-    double *m = nullptr, *ring = nullptr, *Q = nullptr, *part = nullptr;
+    double *m = nullptr, *ring = nullptr, *part = nullptr;
     // fin_h: pinned, coherent host memory the fold kernel writes each read's
     // sums to; ct: the projection's step and radius for its later launches
     double *fin_h = nullptr, *ct = nullptr;
@@ -724,33 +727,43 @@ struct SolveWork {
                           pjs + 2 * rn::PJ_BINS, pjbad, pjst, pjst + 1};
     }
     ~SolveWork() {
-        for (void* p : allocs) (void)hipFree(p);
-        for (void* p : host_allocs) (void)hipHostFree(p);
+        if (arena) (void)hipFree(arena);
+        if (fin_h) (void)hipHostFree(fin_h);
     }
     template <class T>
-    bool alloc(T** out, size_t count) {
-        void* p = nullptr;
-        if (hipMalloc(&p, sizeof(T) * std::max<size_t>(count, 1)) != hipSuccess) {
+    void want(T** out, size_t count) {
+        wanted.push_back({reinterpret_cast<void**>(out), bytes});
+        bytes += (sizeof(T) * std::max<size_t>(count, 1) + 255) / 256 * 256;
+    }
+    // the projection's histograms, first, so that one fill clears them
+    void want_projection() {
+        want(&pjs, PJ_ALL);
+        want(&pjc, PJ_ALL);
+        want(&pjbad, 1);
+        cleared = bytes;
+        want(&ct, 2);
+        want(&pjst, 2);
+    }
+    bool allocate() {
+        if (hipMalloc(&arena, bytes) != hipSuccess) {
             (void)hipGetLastError();
+            arena = nullptr;
             return false;
         }
-        allocs.push_back(p);
-        *out = static_cast<T*>(p);
+        for (auto& w : wanted) *w.first = static_cast<char*>(arena) + w.second;
         return true;
     }
-    bool alloc_host(double** out, size_t count) {
+    bool alloc_host(size_t count) {
         void* p = nullptr;
         if (hipHostMalloc(&p, sizeof(double) * count, hipHostMallocCoherent) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-        host_allocs.push_back(p);
-        *out = static_cast<double*>(p);
+        fin_h = static_cast<double*>(p);
         return true;
     }
+    hipError_t clear(hipStream_t st) const { return hipMemsetAsync(arena, 0, cleared, st); }
 };
-
-std::vector<double> cubic_basis(int N) { return rn::ring_cubic_basis(N); }
 
 // fin slots: 0-1 residual (sum r^2, sum r.b~), 2-4 projection (g.dx, ||xn||_1,
 // the threshold lam), 5-8 spectral step (sum s^2, sum s.y, max |hn|, ||xn||_1)
@@ -792,7 +805,7 @@ struct Solver {
 
     // r = F(b - z) (z may be null) -> fin[0] = sum r^2, fin[1] = sum r.bt (bt may be null)
     void residual(const float* z, float* r, const float* bt) {
-        rn::launch_residual(b, z, filt ? w.Q : nullptr, bt, p.n_views, p.n_det, w.m, w.ring, r, part(FIN_RES), st);
+        rn::launch_residual(b, z, filt ? p.ringQ : nullptr, bt, p.n_views, p.n_det, w.m, w.ring, r, part(FIN_RES), st);
         chk(hipGetLastError());
     }
 
@@ -823,11 +836,7 @@ struct Solver {
     }
     // clear the projection histograms (every projection leaves them cleared;
     // this covers a run that follows one that stopped early)
-    void reset_projection() {
-        chk(hipMemsetAsync(w.pjc, 0, sizeof(unsigned) * SolveWork::PJ_ALL, st));
-        chk(hipMemsetAsync(w.pjs, 0, sizeof(unsigned long long) * SolveWork::PJ_ALL, st));
-        chk(hipMemsetAsync(w.pjbad, 0, sizeof(unsigned), st));
-    }
+    void reset_projection() { chk(w.clear(st)); }
 
     bool forward(const float* x, float* z) {
         ++nf;
@@ -838,14 +847,19 @@ struct Solver {
         return radon_adjoint(plan, r, h, st) == RADON_OK;
     }
 
-    // One line-search trial: xn = P_tau(x + c h), r_n = F(b - A xn),
-    // h_n = A^T r_n, the spectral sums, and fin read back (one host wait)
-    bool trial(double c, double tau, double* fin) {
+    // h_n = A^T r_n and the spectral sums of the trial point
+    bool gradient() {
+        if (!adjoint(w.rn, w.hn)) return false;
+        bb(w.x, w.xn, w.h, w.hn);
+        return true;
+    }
+    // One line-search trial: xn = P_tau(x + c h), r_n = F(b - A xn), its gradient
+    // too if asked, and fin read back (one host wait)
+    bool trial(double c, double tau, bool with_gradient, double* fin) {
         project(w.x, w.h, c, tau, w.xn);
         if (!forward(w.xn, w.z)) return false;
         residual(w.z, w.rn, w.bt);
-        if (!adjoint(w.rn, w.hn)) return false;
-        bb(w.x, w.xn, w.h, w.hn);
+        if (with_gradient && !gradient()) return false;
         return read(fin);
     }
 };
@@ -856,14 +870,12 @@ extern "C" radon_status_t radon_ring_filter(radon_plan_t plan, const float* y_de
     if (!plan || !y_dev || !out_dev) return RADON_ERR_INVALID;
     const rn::Plan& p = plan->p;
     SolveWork w;
-    if (!w.alloc(&w.m, (size_t)rn::CM_CHUNKS * p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
-        !w.alloc(&w.part, (size_t)rn::SV_SLOTS * rn::SV_BLOCKS))
-        return RADON_ERR_OOM;
+    w.want(&w.m, (size_t)rn::CM_CHUNKS * p.n_det);
+    w.want(&w.ring, p.n_det);
+    w.want(&w.part, (size_t)rn::SV_SLOTS * rn::SV_BLOCKS);
+    if (!w.allocate()) return RADON_ERR_OOM;
     hipStream_t st = (hipStream_t)stream;
-    const std::vector<double> Q = cubic_basis(p.n_det);
-    if (hipMemcpy(w.Q, Q.data(), sizeof(double) * Q.size(), hipMemcpyHostToDevice) != hipSuccess)
-        return RADON_ERR_DEVICE;
-    rn::launch_residual(y_dev, nullptr, w.Q, nullptr, p.n_views, p.n_det, w.m, w.ring, out_dev, w.part, st);
+    rn::launch_residual(y_dev, nullptr, p.ringQ, nullptr, p.n_views, p.n_det, w.m, w.ring, out_dev, w.part, st);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return RADON_ERR_DEVICE;
     return RADON_OK;
 }
@@ -882,16 +894,11 @@ extern "C" radon_status_t radon_project_l1(const float* v_dev, int64_t n, double
     if (lam_host) *lam_host = 0.0;
     if (n == 0) return rn::api_ok();
     SolveWork w;
-    if (!w.alloc(&w.part, (size_t)FIN_COUNT * rn::SV_BLOCKS) || !w.alloc(&w.ct, 2) ||
-        !w.alloc(&w.pjc, SolveWork::PJ_ALL) || !w.alloc(&w.pjs, SolveWork::PJ_ALL) || !w.alloc(&w.pjbad, 1) ||
-        !w.alloc(&w.pjst, 2) || !w.alloc_host(&w.fin_h, FIN_COUNT))
-        return rn::api_fail(RADON_ERR_OOM, "radon_project_l1: workspace allocation failed");
+    w.want_projection();
+    w.want(&w.part, 3 * (size_t)rn::SV_BLOCKS);   // the sums of the soft threshold; its third slot holds lam
+    if (!w.allocate()) return rn::api_fail(RADON_ERR_OOM, "radon_project_l1: workspace allocation failed");
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = hipMemsetAsync(w.part, 0, sizeof(double) * FIN_COUNT * rn::SV_BLOCKS, st);
-    if (e == hipSuccess) e = hipMemsetAsync(w.pjc, 0, sizeof(unsigned) * SolveWork::PJ_ALL, st);
-    if (e == hipSuccess) e = hipMemsetAsync(w.pjs, 0, sizeof(unsigned long long) * SolveWork::PJ_ALL, st);
-    if (e == hipSuccess) e = hipMemsetAsync(w.pjbad, 0, sizeof(unsigned), st);
-    if (e != hipSuccess) {
+    if (w.clear(st) != hipSuccess) {
         (void)hipGetLastError();
         return rn::api_fail(RADON_ERR_DEVICE, "radon_project_l1: clearing the workspace failed");
     }
@@ -905,13 +912,16 @@ extern "C" radon_status_t radon_project_l1(const float* v_dev, int64_t n, double
     hipLaunchKernelGGL(rn::k_sv_pj_pass<3>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, 0.0, w.ct,
                        nn, pw);
     hipLaunchKernelGGL(rn::k_sv_soft, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, v_dev, v_dev, w.ct, nn, pw,
-                       out_dev, w.part + (size_t)FIN_PROJ * rn::SV_BLOCKS);
-    hipLaunchKernelGGL(rn::k_sv_final, dim3(1), dim3(rn::SV_NT), 0, st, w.part, FIN_COUNT, FIN_MAX_OPS, w.fin_h);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+                       out_dev, w.part);
+    hipError_t e = hipGetLastError();
+    double lam = 0.0;
+    if (e == hipSuccess && lam_host)
+        e = hipMemcpyAsync(&lam, w.part + 2 * (size_t)rn::SV_BLOCKS, sizeof(double), hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
         (void)hipGetLastError();
         return rn::api_fail(RADON_ERR_DEVICE, "radon_project_l1: launch failed");
     }
-    if (lam_host) *lam_host = w.fin_h[FIN_PROJ + 2];
+    if (lam_host) *lam_host = lam;
     return rn::api_ok();
 }
 
@@ -1086,17 +1096,25 @@ radon_status_t spgl1_run(Solver& S, SolveWork& w, const radon_solve_opts* opts, 
             }
             std::fill(fs.begin(), fs.end(), f);
         }
-        // spectral projected gradient step, non-monotone (GLL) backtracking; the
-        // gradient and spectral sums of each trial point are computed before the
-        // host reads the trial's objective, so an accepted step costs one wait
+        // spectral projected gradient step, non-monotone (GLL) backtracking. The
+        // gradient and spectral sums of the first trial point are computed before
+        // the host reads its objective, so that a step accepted at once (nearly
+        // all are) costs one wait; once one was rejected, only the accepted point's
+        // are computed, after its objective is read. The first step off x = 0 has
+        // no spectral length and backtracks from bb_max, some 28 trials, whose
+        // adjoints were a quarter of a 16-iteration solve at 1024^2, 128 views.
         const double fmax = *std::max_element(fs.begin(), fs.end());
         double step = 1.0, fn = 0, rbtn = 0;
         while (true) {
-            if (!S.trial(step * alpha, tau, fin)) return RADON_ERR_DEVICE;
+            const bool first = step == 1.0;
+            if (!S.trial(step * alpha, tau, first, fin)) return RADON_ERR_DEVICE;
             const double gtd = fin[FIN_PROJ];
             fn = 0.5 * fin[FIN_RES];
             rbtn = fin[FIN_RES + 1];
-            if (fn <= fmax + 1e-4 * gtd || step < 1e-10 || !std::isfinite(fn)) break;
+            if (fn <= fmax + 1e-4 * gtd || step < 1e-10 || !std::isfinite(fn)) {
+                if (!first && std::isfinite(fn) && !(S.gradient() && S.read(fin))) return RADON_ERR_DEVICE;
+                break;
+            }
             step *= 0.5;
         }
         if (!std::isfinite(fn)) {
@@ -1135,17 +1153,15 @@ extern "C" radon_status_t radon_solve_bpdn(radon_plan_t plan, const float* b_dev
     const rn::Plan& p = plan->p;
     SolveWork w;
     const size_t n2 = (size_t)p.n * p.n, ns = (size_t)p.n_views * p.n_det;
-    if (!w.alloc(&w.x, n2) || !w.alloc(&w.xn, n2) || !w.alloc(&w.h, n2) || !w.alloc(&w.hn, n2) ||
-        !w.alloc(&w.z, ns) || !w.alloc(&w.r, ns) || !w.alloc(&w.rn, ns) || !w.alloc(&w.bt, ns) ||
-        !w.alloc(&w.m, (size_t)rn::CM_CHUNKS * p.n_det) || !w.alloc(&w.ring, p.n_det) || !w.alloc(&w.Q, (size_t)p.n_det * 4) ||
-        !w.alloc(&w.part, (size_t)FIN_COUNT * rn::SV_BLOCKS) || !w.alloc(&w.ct, 2) ||
-        !w.alloc(&w.pjc, SolveWork::PJ_ALL) || !w.alloc(&w.pjs, SolveWork::PJ_ALL) || !w.alloc(&w.pjbad, 1) ||
-        !w.alloc(&w.pjst, 2) || !w.alloc_host(&w.fin_h, FIN_COUNT))
-        return RADON_ERR_OOM;
+    w.want_projection();
+    for (float** q : {&w.x, &w.xn, &w.h, &w.hn}) w.want(q, n2);
+    for (float** q : {&w.z, &w.r, &w.rn, &w.bt}) w.want(q, ns);
+    w.want(&w.m, (size_t)rn::CM_CHUNKS * p.n_det);
+    w.want(&w.ring, p.n_det);
+    w.want(&w.part, (size_t)FIN_COUNT * rn::SV_BLOCKS);
+    if (!w.allocate() || !w.alloc_host(FIN_COUNT)) return RADON_ERR_OOM;
     hipStream_t st = (hipStream_t)stream;
     Solver S{plan, p, w, st, opts->ring_filter != 0, b_dev, n2, ns};
-    const std::vector<double> Q = cubic_basis(p.n_det);
-    S.chk(hipMemcpyAsync(w.Q, Q.data(), sizeof(double) * Q.size(), hipMemcpyHostToDevice, st));
     // every read folds all partial slots, also those no kernel has written yet
     S.chk(hipMemsetAsync(w.part, 0, sizeof(double) * FIN_COUNT * rn::SV_BLOCKS, st));
 
