@@ -358,32 +358,30 @@ __device__ __forceinline__ void fft_regs(float2 (&v)[I0][R0], float2* buf, const
     fft_last_to_regs<LEN, B, NT>(buf, tw, tid, out);
 }
 
-// Threads per workgroup used for a transform of B lines of length LEN.
-// Threads for the row/column kernels, whose per-thread register arrays shrink
-// with more threads: 512 from length 1024 on.
-constexpr int line_threads(int len) { return len >= 1024 ? 512 : (len >= 256 ? 256 : (len >= 64 ? 128 : 64)); }
+// Threads of the workgroups, measured per length. Results do not depend on them.
+// Columns (F2, A3: one line per workgroup): a pass of radix 8 has len/8
+// butterflies, so 256 threads keep more lines in flight per CU than 512 up to
+// 2048 (F2 + A3 at 1024: 20.4 us with 256 threads, 24.0 with 512, 21.6 with 128;
+// at 1536 31.9 and 34.6; at 2048 46.1 and 48.2); the registers of 2560 and more
+// points turn that round (80 and 65 us).
+constexpr int line_threads(int len) { return len >= 256 ? 256 : (len >= 64 ? 128 : 64); }
+constexpr int col_threads(int len) { return len > 2048 ? 512 : line_threads(len); }
 
-// Threads of the row kernels (F1, A4) and column kernels (F2, A3) for lines of
-// length 1024 and more (compile-time tuning knobs).
-#ifndef RN_ROW_NT
-#define RN_ROW_NT 1024
-#endif
-#ifndef RN_COL_NT
-#define RN_COL_NT 512
-#endif
-#ifndef RN_RAY_NT
-#define RN_RAY_NT 512
-#endif
-constexpr int row_threads(int len) { return len >= 1024 ? RN_ROW_NT : line_threads(len); }
-constexpr int col_threads(int len) { return len >= 1024 ? RN_COL_NT : line_threads(len); }
+// Rows (F1, A4: `lines` complex lines per workgroup). Half the threads hold the
+// butterflies of 1280 points (F1 + A4 27.7 us with 512, 29.0 with 1024; at 1024
+// points both 21); a single line has the CU to itself and takes more of them.
+constexpr int row_threads(int len, int lines) {
+    return len >= 1024 ? (len == 1280 ? 512 : 1024) : (len >= 256 && lines == 1 ? 512 : line_threads(len));
+}
 
 constexpr int fft_threads(int len, int b) {
     int work = len * b / 8;
     return work >= 1024 ? 512 : (work >= 256 ? 256 : (work >= 128 ? 128 : 64));
 }
-// Threads of the ray kernels (F4, A1: two rays of length len per workgroup).
-// These launches hold only n_views/2 workgroups, so long rays get more
-// threads than their butterfly count asks for: more waves in flight per CU.
-constexpr int ray_threads(int len) { return len >= 2048 ? RN_RAY_NT : fft_threads(len, 1); }
+// Rays (F4, A1: two rays per workgroup). These launches hold only n_views/2
+// workgroups, so the rays get more threads than their butterfly count asks for:
+// more loads in flight per CU (1280 bins: 7.9 us each with 128 threads, 6.4 with
+// 512, between events).
+constexpr int ray_threads(int len) { return len >= 1024 ? 512 : (len >= 256 ? 256 : fft_threads(len, 1)); }
 
 }  // namespace rn

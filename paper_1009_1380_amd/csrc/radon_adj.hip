@@ -86,16 +86,20 @@ hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int L, int LINES>
+static void launch_a4_l(const Plan& p, const Work& w, float* img, hipStream_t st) {
+    constexpr int NT = row_threads(L, LINES);
+    hipLaunchKernelGGL((k_a4_rows<L, NT, LINES>), dim3(row_blocks(L, LINES), w.slices), dim3(NT), 0, st, w.T1, img, p.psi_inv,
+                       p.shift_n, p.tw_n, w.t1_n, w.img_n);
+}
+
 hipError_t launch_a4(const Plan& p, const Work& w, float* img, hipStream_t st) {
-    const dim3 grid(row_blocks(p.n), w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
-    case L: {                                                                                  \
-        constexpr int NT = row_threads(L);                                                   \
-        hipLaunchKernelGGL((k_a4_rows<L, NT>), grid, dim3(NT), 0, st, w.T1, img, p.psi_inv,     \
-                           p.shift_n, p.tw_n, w.t1_n, w.img_n);                                \
-        break;                                                                                 \
-    }
+    case L:                                                                                    \
+        if (w.slices == 1) launch_a4_l<L, row_lines_alone(L)>(p, w, img, st);                  \
+        else launch_a4_l<L, row_lines(L)>(p, w, img, st);                                      \
+        break;
         RN_FOR_LENGTHS(RN_CASE)
 #undef RN_CASE
         default:
@@ -121,7 +125,7 @@ hipError_t launch_pass_adj(PassKind kind, int len, const PassSlice* tab, int ns,
                                    0, st, tab, ns);                                                        \
                 break;                                                                                     \
             case PK_A4:                                                                                    \
-                hipLaunchKernelGGL((k_a4_multi<L, row_threads(L)>), dim3(nblocks), dim3(row_threads(L)),   \
+                hipLaunchKernelGGL((k_a4_multi<L, row_threads(L, row_lines(L))>), dim3(nblocks), dim3(row_threads(L, row_lines(L))),   \
                                    0, st, tab, ns);                                                        \
                 break;                                                                                     \
             default:                                                                                       \

@@ -8,16 +8,20 @@
 
 namespace rn {
 
+template <int L, int LINES>
+static void launch_f1_l(const Plan& p, const Work& w, const float* img, hipStream_t st) {
+    constexpr int NT = row_threads(L, LINES);
+    hipLaunchKernelGGL((k_f1_rows<L, NT, LINES>), dim3(row_blocks(L, LINES), w.slices), dim3(NT), 0, st, img, w.T1, p.psi_inv,
+                       p.shift_n, p.tw_n, w.img_n, w.t1_n);
+}
+
 hipError_t launch_f1(const Plan& p, const Work& w, const float* img, hipStream_t st) {
-    const dim3 grid(row_blocks(p.n), w.slices);
     switch (p.n) {
 #define RN_CASE(L)                                                                             \
-    case L: {                                                                                  \
-        constexpr int NT = row_threads(L);                                                   \
-        hipLaunchKernelGGL((k_f1_rows<L, NT>), grid, dim3(NT), 0, st, img, w.T1, p.psi_inv,     \
-                           p.shift_n, p.tw_n, w.img_n, w.t1_n);                                \
-        break;                                                                                 \
-    }
+    case L:                                                                                    \
+        if (w.slices == 1) launch_f1_l<L, row_lines_alone(L)>(p, w, img, st);                  \
+        else launch_f1_l<L, row_lines(L)>(p, w, img, st);                                      \
+        break;
         RN_FOR_LENGTHS(RN_CASE)
 #undef RN_CASE
         default:
@@ -154,7 +158,7 @@ hipError_t launch_pass_fwd(PassKind kind, int len, const PassSlice* tab, int ns,
     case L:                                                                                                \
         switch (kind) {                                                                                    \
             case PK_F1:                                                                                    \
-                hipLaunchKernelGGL((k_f1_multi<L, row_threads(L)>), dim3(nblocks), dim3(row_threads(L)),   \
+                hipLaunchKernelGGL((k_f1_multi<L, row_threads(L, row_lines(L))>), dim3(nblocks), dim3(row_threads(L, row_lines(L))),   \
                                    0, st, tab, ns);                                                        \
                 break;                                                                                     \
             case PK_F2:                                                                                    \
@@ -190,12 +194,12 @@ PassSlice pass_slice_of(const Plan& p, PassKind kind, const void* in, void* out)
     e.shift = p.shift_n;
     e.wq = nullptr;
     switch (kind) {
-        case PK_F1: e.nblk = row_blocks(p.n); e.in = in; e.out = p.T1; e.tw = p.tw_n; break;
+        case PK_F1: e.nblk = row_blocks(p.n, row_lines(p.n)); e.in = in; e.out = p.T1; e.tw = p.tw_n; break;
         case PK_F2: e.nblk = p.n + 1; e.in = p.T1; e.out = p.grid; e.tw = p.tw_n; break;
         case PK_F4: e.nblk = (p.n_views + 1) / 2; e.in = p.Xr; e.out = out; e.tw = p.tw_N; break;
         case PK_A1: e.nblk = (p.n_views + 1) / 2; e.in = in; e.out = p.Yh; e.tw = p.tw_N; break;
         case PK_A3: e.nblk = p.n + 1; e.in = p.grid; e.out = p.T1; e.tw = p.tw_n; break;
-        case PK_A4: e.nblk = row_blocks(p.n); e.in = p.T1; e.out = out; e.tw = p.tw_n; break;
+        case PK_A4: e.nblk = row_blocks(p.n, row_lines(p.n)); e.in = p.T1; e.out = out; e.tw = p.tw_n; break;
     }
     return e;
 }

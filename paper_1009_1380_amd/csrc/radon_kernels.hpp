@@ -132,14 +132,19 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // one workgroup per CU).
 // With two lines, 2560 rows make 640 workgroups, two resident per CU, and a
 // fifth of them ran in a second round.
+// A launch of one slice of up to 768 rows takes one line, since with two some
+// CUs would have no workgroup (F1 + A4 at 512 rows 18.3 us with two lines, 16.4
+// with one; at 768 21.8 and 19.0); launches of several slices fill the chip and
+// keep two (8 slices of 512 rows, forward and adjoint: 99 us against 107).
 constexpr int row_lines(int len) { return (len == 2048 || len == 2560) ? len / 512 : 2; }
 // Waves per SIMD the row kernels are compiled for: with 1024 threads and two
 // lines, 8 holds two workgroups on a CU (at most 64 VGPRs per lane), which
 // lines of up to 2560 points fit without spilling; one workgroup per CU
 // needs 4.
-constexpr int row_waves(int len) { return row_lines(len) > 2 ? 4 : (len <= 2560 ? 8 : 4); }
+constexpr int row_waves(int len, int lines) { return lines > 2 ? 4 : (len <= 2560 ? 8 : 4); }
+constexpr int row_lines_alone(int len) { return len <= 768 ? 1 : row_lines(len); }
 // workgroups of a row pass over n rows
-constexpr int row_blocks(int n) { return (n + 2 * row_lines(n) - 1) / (2 * row_lines(n)); }
+constexpr int row_blocks(int n, int lines) { return (n + 2 * lines - 1) / (2 * lines); }
 
 template <int NL, int NT>
 __device__ __forceinline__ void f1_store(float2* __restrict__ T1, const float2* lds, int m, int k, int kc, int i0,
@@ -157,13 +162,12 @@ __device__ __forceinline__ void f1_store(float2* __restrict__ T1, const float2* 
     if (i0 + 2 * p + 1 < NL) *reinterpret_cast<float4*>(dst) = make_float4(o0.x, o0.y, o1.x, o1.y);
 }
 
-template <int NL, int NT>
+template <int NL, int NT, int NLN>
 __device__ __forceinline__ void f1_body(int bid_, int nblk_, const float* __restrict__ img, float2* __restrict__ T1,
                                                const float* __restrict__ psi_inv,
                                                const float2* __restrict__ shift,
                                                const float2* __restrict__ tw) {
     constexpr int LS = lds_ls(NL);
-    constexpr int NLN = row_lines(NL);
     __shared__ float2 lds[NLN * LS];
     const int tid = threadIdx.x;
     const int i0 = 2 * NLN * xcd_block(bid_, nblk_);
@@ -1066,13 +1070,12 @@ __device__ __forceinline__ void a4_load(const float2* __restrict__ T1, float2* l
     }
 }
 
-template <int NL, int NT>
+template <int NL, int NT, int NLN>
 __device__ __forceinline__ void a4_body(int bid_, int nblk_, const float2* __restrict__ T1, float* __restrict__ img,
                                                const float* __restrict__ psi_inv,
                                                const float2* __restrict__ shift,
                                                const float2* __restrict__ tw) {
     constexpr int LS = lds_ls(NL);
-    constexpr int NLN = row_lines(NL);
     __shared__ float2 lds[NLN * LS];
     const int tid = threadIdx.x;
     const int i0 = 2 * NLN * xcd_block(bid_, nblk_);
@@ -1168,11 +1171,11 @@ __device__ __forceinline__ void a4_body(int bid_, int nblk_, const float2* __res
 // blockIdx.y (z for the split-strip sums) is the slice, whose buffers lie `is`
 // and `os` elements after the previous slice's (batches of uneven slices use
 // radon_multi.hpp's kernels, which run the same bodies).
-template <int NL, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_f1_rows(
+template <int NL, int NT, int NLN>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL, NLN)))) void k_f1_rows(
     const float* __restrict__ img, float2* __restrict__ T1, const float* __restrict__ psi_inv,
     const float2* __restrict__ shift, const float2* __restrict__ tw, size_t is, size_t os) {
-    f1_body<NL, NT>(blockIdx.x, gridDim.x, img + blockIdx.y * is, T1 + blockIdx.y * os, psi_inv, shift, tw);
+    f1_body<NL, NT, NLN>(blockIdx.x, gridDim.x, img + blockIdx.y * is, T1 + blockIdx.y * os, psi_inv, shift, tw);
 }
 
 template <int NL, int NT>
@@ -1250,11 +1253,11 @@ __global__ __launch_bounds__(NT) void k_a3_cols(const float2* __restrict__ grid,
     a3_body<NL, NT>(blockIdx.x, gridDim.x, grid + blockIdx.y * is, T1 + blockIdx.y * os, shift, tw);
 }
 
-template <int NL, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_a4_rows(
+template <int NL, int NT, int NLN>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL, NLN)))) void k_a4_rows(
     const float2* __restrict__ T1, float* __restrict__ img, const float* __restrict__ psi_inv,
     const float2* __restrict__ shift, const float2* __restrict__ tw, size_t is, size_t os) {
-    a4_body<NL, NT>(blockIdx.x, gridDim.x, T1 + blockIdx.y * is, img + blockIdx.y * os, psi_inv, shift, tw);
+    a4_body<NL, NT, NLN>(blockIdx.x, gridDim.x, T1 + blockIdx.y * is, img + blockIdx.y * os, psi_inv, shift, tw);
 }
 
 // ---------------------------------------------------------------- FFT test

@@ -47,10 +47,10 @@ __device__ __forceinline__ int pass_slice(const PassSlice* __restrict__ tab, int
 }
 
 template <int NL, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_f1_multi(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL, row_lines(NL))))) void k_f1_multi(
     const PassSlice* __restrict__ tab, int ns) {
     const PassSlice e = tab[pass_slice(tab, ns, blockIdx.x)];
-    f1_body<NL, NT>(blockIdx.x - e.block0, e.nblk, (const float*)e.in, (float2*)e.out, e.psi_inv, e.shift, e.tw);
+    f1_body<NL, NT, row_lines(NL)>(blockIdx.x - e.block0, e.nblk, (const float*)e.in, (float2*)e.out, e.psi_inv, e.shift, e.tw);
 }
 
 template <int NL, int NT>
@@ -78,10 +78,10 @@ __global__ __launch_bounds__(NT) void k_a3_multi(const PassSlice* __restrict__ t
 }
 
 template <int NL, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL)))) void k_a4_multi(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(row_waves(NL, row_lines(NL))))) void k_a4_multi(
     const PassSlice* __restrict__ tab, int ns) {
     const PassSlice e = tab[pass_slice(tab, ns, blockIdx.x)];
-    a4_body<NL, NT>(blockIdx.x - e.block0, e.nblk, (const float2*)e.in, (float*)e.out, e.psi_inv, e.shift, e.tw);
+    a4_body<NL, NT, row_lines(NL)>(blockIdx.x - e.block0, e.nblk, (const float2*)e.in, (float*)e.out, e.psi_inv, e.shift, e.tw);
 }
 
 // The gridding buffers of one slice.
