@@ -1,5 +1,5 @@
 // radon_adj.hip - launchers of the adjoint path (A1 ray FFT, A2 binned
-// spreading + split-tile reduction, A3 column inverse FFT, A4 row inverse FFT),
+// spreading, A3 split-tile sums + column inverse FFT, A4 row inverse FFT),
 // dispatched on the FFT length, kernel width and tile size.
 #include "radon_internal.hpp"
 
@@ -51,21 +51,23 @@ hipError_t launch_a2(const Plan& p, const Work& w, hipStream_t st) {
     }
 }
 
-template <int T>
-static hipError_t launch_a2_reduce_t(const Plan& p, const Work& w, hipStream_t st) {
-    hipLaunchKernelGGL((k_a2_reduce<T>), dim3(p.n_splits, (A2_GX * T * T + 255) / 256, w.slices), dim3(256), 0, st, p.splits,
-                       w.partials, w.grid, p.G, w.grid_n, w.part_n);
-    return hipGetLastError();
+SplitSums split_sums_of(const Plan& p, const float2* partials) {
+    return SplitSums{p.splits, p.split_cols, partials, p.T == 32 ? 5 : (p.T == 16 ? 4 : 3)};
 }
 
-hipError_t launch_a2_reduce(const Plan& p, const Work& w, hipStream_t st) {
-    if (p.n_splits == 0) return hipSuccess;
-    switch (p.T) {
-        case 8: return launch_a2_reduce_t<8>(p, w, st);
-        case 16: return launch_a2_reduce_t<16>(p, w, st);
-        case 32: return launch_a2_reduce_t<32>(p, w, st);
-        default: return hipErrorInvalidValue;
+hipError_t launch_split_sums(const Plan& p, const Work& w, hipStream_t st) {
+    switch (p.n) {
+#define RN_CASE(L)                                                                             \
+    case L:                                                                                    \
+        hipLaunchKernelGGL((k_split_sums<L, col_threads(L)>), dim3(p.n + 1), dim3(col_threads(L)), 0, st, w.grid, \
+                           split_sums_of(p, w.partials));                                      \
+        break;
+        RN_FOR_LENGTHS(RN_CASE)
+#undef RN_CASE
+        default:
+            return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st) {
@@ -74,8 +76,8 @@ hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st) {
 #define RN_CASE(L)                                                                             \
     case L: {                                                                                  \
         constexpr int NT = col_threads(L);                                                   \
-        hipLaunchKernelGGL((k_a3_cols<L, NT>), grid, dim3(NT), 0, st, w.grid, w.T1, p.shift_n,  \
-                           p.tw_n, w.grid_n, w.t1_n);                                          \
+        hipLaunchKernelGGL((k_a3_cols<L, NT>), grid, dim3(NT), 0, st, w.grid, split_sums_of(p, w.partials), \
+                           w.T1, p.shift_n, p.tw_n, w.grid_n, w.part_n, w.t1_n);               \
         break;                                                                                 \
     }
         RN_FOR_LENGTHS(RN_CASE)
@@ -141,33 +143,27 @@ hipError_t launch_pass_adj(PassKind kind, int len, const PassSlice* tab, int ns,
 }
 
 template <int W, int T>
-static hipError_t launch_a2m_wt(const GridLaunch& g, const GridSlice* gs, bool reduce, hipStream_t st) {
-    if (!reduce) {
-        if (g.n_items == 0) return hipSuccess;
-        hipLaunchKernelGGL((k_a2_multi<W, T>), dim3(g.n_items), dim3(A2_NT), 0, st, g.items, gs, g.kbc);
-    } else {
-        if (g.n_splits == 0) return hipSuccess;
-        hipLaunchKernelGGL((k_a2r_multi<T>), dim3(g.n_splits, (A2_GX * T * T + 255) / 256), dim3(256), 0, st,
-                           g.splits, gs);
-    }
+static hipError_t launch_a2m_wt(const GridLaunch& g, const GridSlice* gs, hipStream_t st) {
+    if (g.n_items == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_a2_multi<W, T>), dim3(g.n_items), dim3(A2_NT), 0, st, g.items, gs, g.kbc);
     return hipGetLastError();
 }
 
 template <int W>
-static hipError_t launch_a2m_w(const GridLaunch& g, const GridSlice* gs, bool reduce, hipStream_t st) {
+static hipError_t launch_a2m_w(const GridLaunch& g, const GridSlice* gs, hipStream_t st) {
     switch (g.T) {
-        case 8: return launch_a2m_wt<W, 8>(g, gs, reduce, st);
-        case 16: return launch_a2m_wt<W, 16>(g, gs, reduce, st);
-        case 32: return launch_a2m_wt<W, 32>(g, gs, reduce, st);
+        case 8: return launch_a2m_wt<W, 8>(g, gs, st);
+        case 16: return launch_a2m_wt<W, 16>(g, gs, st);
+        case 32: return launch_a2m_wt<W, 32>(g, gs, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_a2_grid(const GridLaunch& g, const GridSlice* gs, bool reduce, hipStream_t st) {
+hipError_t launch_a2_grid(const GridLaunch& g, const GridSlice* gs, hipStream_t st) {
     switch (g.W) {
-        case 4: return launch_a2m_w<4>(g, gs, reduce, st);
-        case 6: return launch_a2m_w<6>(g, gs, reduce, st);
-        case 8: return launch_a2m_w<8>(g, gs, reduce, st);
+        case 4: return launch_a2m_w<4>(g, gs, st);
+        case 6: return launch_a2m_w<6>(g, gs, st);
+        case 8: return launch_a2m_w<8>(g, gs, st);
         default: return hipErrorInvalidValue;
     }
 }

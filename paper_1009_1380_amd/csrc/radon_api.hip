@@ -232,8 +232,6 @@ radon_status_t run_adjoint_grid(Plan& p, const rn::Work& w, const float* sino, h
     if ((s = launch_status(staged(p, rn::ST_A1, st, [&] { return rn::launch_a1(p, w, sino, filtered, st); }), "A1")))
         return s;
     if ((s = launch_status(staged(p, rn::ST_A2, st, [&] { return rn::launch_a2(p, w, st); }), "A2"))) return s;
-    if (p.n_splits > 0)
-        if ((s = launch_status(staged(p, rn::ST_A2R, st, [&] { return rn::launch_a2_reduce(p, w, st); }), "A2 reduce"))) return s;
     return RADON_OK;
 }
 
@@ -386,7 +384,7 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
                 items.push_back({cx, cy, 0, total, -1, gx, 0, 0});
             } else {
                 const int nch = (total + chunk - 1) / chunk;
-                splits.push_back({cx, cy, slots, nch, gx, 0});
+                splits.push_back({cx, cy, slots, nch});
                 for (int k = 0; k < nch; ++k)
                     items.push_back({cx, cy, k * chunk, std::min(chunk, total - k * chunk), slots + k, gx, 0, 0});
                 slots += nch;
@@ -446,7 +444,6 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
     p.n_fitems = (int)fitems.size();
     p.items_h = items;
     p.fitems_h = fitems;
-    p.splits_h = splits;
     {
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p.device) != hipSuccess || cus < 1) {
@@ -456,7 +453,11 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
         p.f3_resident = std::max(1, rn::f3_blocks_per_cu(p.W, p.T) * cus);
         p.f3_grid = std::max(1, std::min(p.n_fitems, p.f3_resident));
     }
-    p.n_splits = (int)splits.size();
+    std::stable_sort(splits.begin(), splits.end(),
+                     [](const rn::SplitTile& a, const rn::SplitTile& b) { return a.cx < b.cx; });
+    std::vector<int> split_cols(ntl + 1, 0);
+    for (const rn::SplitTile& t : splits) ++split_cols[t.cx + 1];
+    for (int c = 0; c < ntl; ++c) split_cols[c + 1] += split_cols[c];
     p.n_slots = slots;
     radon_status_t s;
     if ((s = dev_alloc(p, &p.items, items.size()))) return s;
@@ -465,6 +466,7 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
     if (!fitems.empty() && (s = upload(p.fitems, fitems))) return s;
     if ((s = dev_alloc(p, &p.splits, splits.size()))) return s;
     if (!splits.empty() && (s = upload(p.splits, splits))) return s;
+    if ((s = dev_alloc(p, &p.split_cols, split_cols.size())) || (s = upload(p.split_cols, split_cols))) return s;
     if ((s = dev_alloc(p, &p.partials, (size_t)std::max(slots, 1) * rn::A2_GX * p.T * p.T))) return s;
     return RADON_OK;
 }
@@ -841,6 +843,7 @@ radon_status_t radon_debug_adjoint_grid(radon_plan_t plan, const float* sino_dev
     const bool prof = p.profiling;
     p.profiling = false;
     s = run_adjoint_grid(p, rn::plan_work(p), sino_dev, st);
+    if (!s) s = launch_status(rn::launch_split_sums(p, rn::plan_work(p), st), "split sums");
     p.profiling = prof;
     if (s) return s;
     if (hipMemcpyAsync(grid_dev, p.grid, sizeof(float2) * (size_t)(p.n + 1) * p.G, hipMemcpyDeviceToDevice, st) !=

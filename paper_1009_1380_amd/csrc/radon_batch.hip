@@ -156,30 +156,25 @@ struct radon_batch_s {
             g.T = wt.second;
             std::vector<rn::F3Item> fi;
             std::vector<rn::TileItem> ti;
-            std::vector<rn::SplitTile> sp;
             for (int i = 0; i < P; ++i) {
                 const rn::Plan& p = plans[i]->p;
                 if (p.W != g.W || p.T != g.T) continue;
                 if (!g.kbc) g.kbc = p.kbc;   // the same table for every slice of one W
                 for (rn::F3Item it : p.fitems_h) { it.plan = i; fi.push_back(it); }
                 for (rn::TileItem it : p.items_h) { it.plan = i; ti.push_back(it); }
-                for (rn::SplitTile st : p.splits_h) { st.plan = i; sp.push_back(st); }
             }
             // longest first, so the tail of each launch is short
             std::stable_sort(fi.begin(), fi.end(), [](const rn::F3Item& a, const rn::F3Item& b) { return a.count > b.count; });
             std::stable_sort(ti.begin(), ti.end(), [](const rn::TileItem& a, const rn::TileItem& b) { return a.count > b.count; });
             g.n_fitems = (int)fi.size();
             g.n_items = (int)ti.size();
-            g.n_splits = (int)sp.size();
             g.f3_grid = std::max(1, std::min(g.n_fitems, rn::f3_blocks_per_cu(g.W, g.T) * cus));
             rn::F3Item* dfi = nullptr;
             rn::TileItem* dti = nullptr;
-            rn::SplitTile* dsp = nullptr;
-            if (!upload_vec(owned, &dfi, fi) || !upload_vec(owned, &dti, ti) || !upload_vec(owned, &dsp, sp))
+            if (!upload_vec(owned, &dfi, fi) || !upload_vec(owned, &dti, ti))
                 return errf(RADON_ERR_OOM, "batch work-list upload failed");
             g.fitems = dfi;
             g.items = dti;
-            g.splits = dsp;
             groups.push_back(GridGroup{g});
         }
         return RADON_OK;
@@ -222,7 +217,7 @@ struct radon_batch_s {
 
     // Record one direction for these I/O pointers into rec's graph:
     //   forward: F1 -> F2 per image size (one branch each), F3 per (W, T), F4 per detector count
-    //   adjoint: A1 per detector count, A2 (+ split sums) per (W, T), A3 -> A4 per image size
+    //   adjoint: A1 per detector count, A2 per (W, T), A3 (with the split sums) -> A4 per image size
     radon_status_t record(bool forward, const float* const* in, float* const* out, Recording& rec) {
         rec.release();
         std::vector<PassSlice> tab;
@@ -272,10 +267,8 @@ struct radon_batch_s {
             fork();
             for (size_t g = 0; g < nl_nd; ++g) run(launches[g], streams[g % nb]);
             join();
-            for (const GridGroup& g : groups) {
-                if (e == hipSuccess) e = rn::launch_a2_grid(g.launch, gs, false, s0);
-                if (e == hipSuccess) e = rn::launch_a2_grid(g.launch, gs, true, s0);
-            }
+            for (const GridGroup& g : groups)
+                if (e == hipSuccess) e = rn::launch_a2_grid(g.launch, gs, s0);
             fork();
             for (size_t g = 0; g < nl_n; ++g) {
                 hipStream_t s = streams[g % nb];

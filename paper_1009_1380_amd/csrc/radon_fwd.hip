@@ -198,7 +198,7 @@ PassSlice pass_slice_of(const Plan& p, PassKind kind, const void* in, void* out)
         case PK_F2: e.nblk = p.n + 1; e.in = p.T1; e.out = p.grid; e.tw = p.tw_n; break;
         case PK_F4: e.nblk = (p.n_views + 1) / 2; e.in = p.Xr; e.out = out; e.tw = p.tw_N; break;
         case PK_A1: e.nblk = (p.n_views + 1) / 2; e.in = in; e.out = p.Yh; e.tw = p.tw_N; break;
-        case PK_A3: e.nblk = p.n + 1; e.in = p.grid; e.out = p.T1; e.tw = p.tw_n; break;
+        case PK_A3: e.nblk = p.n + 1; e.in = p.grid; e.out = p.T1; e.tw = p.tw_n; e.sums = split_sums_of(p, p.partials); break;
         case PK_A4: e.nblk = row_blocks(p.n, row_lines(p.n)); e.in = p.T1; e.out = out; e.tw = p.tw_n; break;
     }
     return e;

@@ -43,7 +43,7 @@ struct Plan {
     double sigma = 0, beta = 0;
     int64_t n_samples = 0;   // real samples + mirrored Nyquist samples
     int n_bins = 0;                     // tiles; the sort has 4 edge classes per tile
-    int n_items = 0, n_slots = 0, n_splits = 0;   // spreading work
+    int n_items = 0, n_slots = 0;   // spreading work
     int n_fitems = 0;                   // forward interpolation work
     int f3_grid = 0;                    // workgroups of the persistent forward interpolation
     int f3_resident = 0;                // forward interpolation workgroups that fit on the device
@@ -69,6 +69,7 @@ struct Plan {
     F3Item* fitems = nullptr;
     TileItem* items = nullptr;
     SplitTile* splits = nullptr;
+    int* split_cols = nullptr;   // first split of each tile column, ntl + 1
     float2* partials = nullptr;
     // workspace of several slices at a time (radon_forward_batched and
     // radon_adjoint_batched), allocated by the first call that uses it
@@ -77,7 +78,6 @@ struct Plan {
     // host copies of the work lists (batches concatenate them across slices)
     std::vector<TileItem> items_h;
     std::vector<F3Item> fitems_h;
-    std::vector<SplitTile> splits_h;
     size_t bytes = 0;
     std::vector<void*> allocs;
     int n_allocs = 0;        // device allocations made while building the plan
@@ -108,7 +108,8 @@ int f3_blocks_per_cu(int W, int T);   // resident forward-interpolation workgrou
 hipError_t launch_f4(const Plan& p, const Work& w, float* sino, hipStream_t st);
 hipError_t launch_a1(const Plan& p, const Work& w, const float* sino, bool filtered, hipStream_t st);
 hipError_t launch_a2(const Plan& p, const Work& w, hipStream_t st);
-hipError_t launch_a2_reduce(const Plan& p, const Work& w, hipStream_t st);
+hipError_t launch_split_sums(const Plan& p, const Work& w, hipStream_t st);   // one slice
+SplitSums split_sums_of(const Plan& p, const float2* partials);
 hipError_t launch_a3(const Plan& p, const Work& w, hipStream_t st);
 hipError_t launch_a4(const Plan& p, const Work& w, float* img, hipStream_t st);
 // Launchers for uneven batches (radon_multi.hpp): one transform pass over the
@@ -120,8 +121,6 @@ struct GridLaunch {
     int n_fitems, f3_grid;
     const TileItem* items;
     int n_items;
-    const SplitTile* splits;
-    int n_splits;
     const float4* kbc;
 };
 PassSlice pass_slice_of(const Plan& p, PassKind kind, const void* in, void* out);
@@ -130,7 +129,7 @@ hipError_t launch_pass(PassKind kind, int len, const PassSlice* tab, int ns, int
 hipError_t launch_pass_fwd(PassKind kind, int len, const PassSlice* tab, int ns, int nblocks, hipStream_t st);
 hipError_t launch_pass_adj(PassKind kind, int len, const PassSlice* tab, int ns, int nblocks, hipStream_t st);
 hipError_t launch_f3_grid(const GridLaunch& g, const GridSlice* gs, hipStream_t st);
-hipError_t launch_a2_grid(const GridLaunch& g, const GridSlice* gs, bool reduce, hipStream_t st);
+hipError_t launch_a2_grid(const GridLaunch& g, const GridSlice* gs, hipStream_t st);
 
 hipError_t launch_fft_test(int len, int batch, int inverse, const float2* in, float2* out,
                            const float2* tw, hipStream_t st);

@@ -921,57 +921,69 @@ __device__ __forceinline__ void a2_item(const TileItem& it, const SampleRec* __r
     }
 }
 
-// Sum the partial strips of split output strips in slot order.
+// A split output strip (always one tile): its partial sums are slots
+// first_slot .. first_slot + nslots - 1 of A2_GX T T points each, [lx][ly].
+// Sorted by tile column.
 struct SplitTile {
     int cx, cy;
     int first_slot, nslots;
-    int gx;          // tile columns of the strip
-    int plan;        // batches: index of the strip's plan in the batch (else 0)
+};
+// What the pass after the spreading needs to add them up.
+struct SplitSums {
+    const SplitTile* splits;
+    const int* cols;            // first split of each tile column, and their count last
+    const float2* partials;
+    int tile_log2;
 };
 
-#ifndef RN_A2R_FLIGHT
-#define RN_A2R_FLIGHT 16
-#endif
-template <int T>
-__device__ __forceinline__ void a2r_body(const SplitTile& sp, int by, const float2* __restrict__ partials,
-                                         float2* __restrict__ grid, int G) {
-    constexpr int SLOT = A2_GX * T * T;   // points per partial slot
-    const int xvalid = (sp.cx == 0) ? 1 : sp.gx * T;   // tile column 0 holds only mx = G/2
-    const int x0 = sp.cx * T, y0 = sp.cy * T;
-    const int my0 = mod_pos(y0 - G / 2, G);
-    const float2* src = partials + (size_t)sp.first_slot * SLOT;
-    // block row `by` picks 256 of the strip's points, one per thread
-    for (int e = by * 256 + threadIdx.x; e < xvalid * T && e < (by + 1) * 256; e += 256) {
-        // slots are added in order; the loads of RN_A2R_FLIGHT slots (the last batch
-        // predicated) are issued together
-        float2 s = make_float2(0.f, 0.f);
-        for (int k = 0; k < sp.nslots; k += RN_A2R_FLIGHT) {
-            float2 v[RN_A2R_FLIGHT];
+// Grid line mx (of G = 2 NL points) from the partial sums of the split strips it
+// crosses, added in slot order, for the workgroup that reads the line next: two
+// consecutive my per lane, A2R_FLIGHT slots in flight. A pass of its own costs a
+// launch and the grid's round trip (forward and adjoint of 128 rows, 180 views 38.9 us
+// with it, 37.3 without; 512 and 90 47.0 and 45.3; 1024 and 360 72.6 and 70.0;
+// 2560 and 1024 220.6 and 219.3).
+constexpr int A2R_FLIGHT = 8;
+template <int NL, int NT>
+__device__ __forceinline__ void split_sums(int mx, const SplitSums& sp, const float2* __restrict__ partials, float2* grid) {
+    const int tl = sp.tile_log2, T = 1 << tl;
+    const int ux = mx == NL ? 0 : mx + NL;          // centred coordinate; tile column 0 holds only mx = G/2
+    const int cx = ux >> tl, lx = ux & (T - 1);
+    const int s0 = sp.cols[cx], s1 = sp.cols[cx + 1];
+    if (s0 == s1) return;
+    const size_t slot = (size_t)A2_GX * T * T;
+    for (int e = threadIdx.x; e < (s1 - s0) << (tl - 1); e += NT) {
+        const SplitTile st = sp.splits[s0 + (e >> (tl - 1))];
+        const int ly = 2 * (e & (T / 2 - 1));
+        const float2* src = partials + st.first_slot * slot + (lx << tl) + ly;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k = 0; k < st.nslots; k += A2R_FLIGHT) {
+            float4 v[A2R_FLIGHT];
 #pragma unroll
-            for (int j = 0; j < RN_A2R_FLIGHT; ++j)
-                v[j] = (k + j < sp.nslots) ? src[(size_t)(k + j) * SLOT + e] : make_float2(0.f, 0.f);
+            for (int j = 0; j < A2R_FLIGHT; ++j)
+                if (k + j < st.nslots) v[j] = *reinterpret_cast<const float4*>(src + (k + j) * slot);
 #pragma unroll
-            for (int j = 0; j < RN_A2R_FLIGHT; ++j)
-                if (k + j < sp.nslots) s = (k + j == 0) ? v[j] : cadd(s, v[j]);
+            for (int j = 0; j < A2R_FLIGHT; ++j)
+                if (k + j < st.nslots)
+                    s = (k + j == 0) ? v[j] : make_float4(s.x + v[j].x, s.y + v[j].y, s.z + v[j].z, s.w + v[j].w);
         }
-        const int lx = e / T, ly = e - lx * T;
-        const int mx = wrap_g(x0 + lx - G / 2, G);
-        grid[(size_t)mx * G + my0 + ly] = s;
+        *reinterpret_cast<float4*>(grid + (size_t)mx * (2 * NL) + wrap_g((st.cy << tl) - NL, 2 * NL) + ly) = s;
     }
+    __syncthreads();   // the line's other lanes read these points from memory
 }
 
 // ---------------------------------------------------------------- A3
-// One grid line mx per workgroup: h[p] = sum_my H[my] e^{+2 pi i my p/G} for
+// One grid line mx per workgroup, first completed from the partial sums of split
+// strips (split_sums): h[p] = sum_my H[my] e^{+2 pi i my p/G} for
 // the n rows p = -n/2..n/2-1 = IFFT_n(H_even)[p] + e^{i pi p/n} IFFT_n(H_odd)[p];
 // the two inverse transforms share one LDS line, one after the other, each
 // with register input and output (FftRegIO); the inverse is conj(FFT(conj)).
 template <int NL, int NT>
-__device__ __forceinline__ void a3_body(int bid_, int nblk_, const float2* __restrict__ grid, float2* __restrict__ T1,
-                                               const float2* __restrict__ shift,
-                                               const float2* __restrict__ tw) {
+__device__ __forceinline__ void a3_body(int mx, float2* grid, const SplitSums& sp, const float2* __restrict__ partials,
+                                        float2* __restrict__ T1, const float2* __restrict__ shift,
+                                        const float2* __restrict__ tw) {
     __shared__ float2 lds[lds_ls(NL)];
     const int tid = threadIdx.x;
-    const int mx = bid_;
+    split_sums<NL, NT>(mx, sp, partials, grid);
     const float4* src = reinterpret_cast<const float4*>(grid + (size_t)mx * (2 * NL));
     float2* dst = T1 + (size_t)mx * NL;
     using IO = FftRegIO<NL, 1, NT>;
@@ -1168,7 +1180,7 @@ __device__ __forceinline__ void a4_body(int bid_, int nblk_, const float2* __res
 
 // ---------------------------------------------------------------- one plan's kernels
 // One launch per pass of one slice, or of several slices that share a plan:
-// blockIdx.y (z for the split-strip sums) is the slice, whose buffers lie `is`
+// blockIdx.y is the slice, whose buffers lie `is`
 // and `os` elements after the previous slice's (batches of uneven slices use
 // radon_multi.hpp's kernels, which run the same bodies).
 template <int NL, int NT, int NLN>
@@ -1238,19 +1250,17 @@ __global__ __launch_bounds__(A2_NT) __attribute__((amdgpu_waves_per_eu(W <= 6 ? 
     a2_item<W, T>(it, recs, Yh + blockIdx.y * is, kbc, grid + blockIdx.y * os, partials + blockIdx.y * ps, G);
 }
 
-template <int T>
-__global__ __launch_bounds__(256) void k_a2_reduce(const SplitTile* __restrict__ splits,
-                                                  const float2* __restrict__ partials, float2* __restrict__ grid,
-                                                  int G, size_t os, size_t ps) {
-    const SplitTile sp = splits[blockIdx.x];
-    a2r_body<T>(sp, blockIdx.y, partials + blockIdx.z * ps, grid + blockIdx.z * os, G);
+template <int NL, int NT>
+__global__ __launch_bounds__(NT) void k_a3_cols(float2* grid, SplitSums sp, float2* __restrict__ T1,
+                                               const float2* __restrict__ shift, const float2* __restrict__ tw,
+                                               size_t is, size_t ps, size_t os) {
+    a3_body<NL, NT>(blockIdx.x, grid + blockIdx.y * is, sp, sp.partials + blockIdx.y * ps, T1 + blockIdx.y * os, shift, tw);
 }
 
+// The split sums alone (the spread grid without the passes that follow).
 template <int NL, int NT>
-__global__ __launch_bounds__(NT) void k_a3_cols(const float2* __restrict__ grid, float2* __restrict__ T1,
-                                               const float2* __restrict__ shift, const float2* __restrict__ tw,
-                                               size_t is, size_t os) {
-    a3_body<NL, NT>(blockIdx.x, gridDim.x, grid + blockIdx.y * is, T1 + blockIdx.y * os, shift, tw);
+__global__ __launch_bounds__(NT) void k_split_sums(float2* grid, SplitSums sp) {
+    split_sums<NL, NT>(blockIdx.x, sp, sp.partials, grid);
 }
 
 template <int NL, int NT, int NLN>

@@ -27,6 +27,7 @@ struct PassSlice {
     int nblk;               // blocks of the slice
     int n_views;
     int pad;
+    SplitSums sums;         // A3: the slice's split strips
     const void* in;         // the pass's input (image, T1, grid, Xr or sinogram)
     void* out;              // its output
     const float* psi_inv;   // 1/psi1, n
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(NT) void k_a1_multi(const PassSlice* __restrict__ t
 template <int NL, int NT>
 __global__ __launch_bounds__(NT) void k_a3_multi(const PassSlice* __restrict__ tab, int ns) {
     const PassSlice e = tab[pass_slice(tab, ns, blockIdx.x)];
-    a3_body<NL, NT>(blockIdx.x - e.block0, e.nblk, (const float2*)e.in, (float2*)e.out, e.shift, e.tw);
+    a3_body<NL, NT>(blockIdx.x - e.block0, (float2*)e.in, e.sums, e.sums.partials, (float2*)e.out, e.shift, e.tw);
 }
 
 template <int NL, int NT>
@@ -119,14 +120,6 @@ __global__ __launch_bounds__(A2_NT) __attribute__((amdgpu_waves_per_eu(W <= 6 ? 
     const TileItem it = items[blockIdx.x];
     const GridSlice g = gs[it.plan];
     a2_item<W, T>(it, g.recs, g.Yh, kbc, g.grid, g.partials, g.G);
-}
-
-template <int T>
-__global__ __launch_bounds__(256) void k_a2r_multi(const SplitTile* __restrict__ splits,
-                                                  const GridSlice* __restrict__ gs) {
-    const SplitTile sp = splits[blockIdx.x];
-    const GridSlice g = gs[sp.plan];
-    a2r_body<T>(sp, blockIdx.y, g.partials, g.grid, g.G);
 }
 
 }  // namespace rn
