@@ -360,38 +360,56 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
     for (int cx = std::max(ntl / 2, 1); cx < ntl; cx += rn::A2_GX) strips.push_back({cx, std::min(rn::A2_GX, ntl - cx)});
     strips.push_back({0, 1});
     int slots = 0;
-    const int chunk = p.a2_chunk;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p.device) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        cus = 1;
+    }
     auto strip_total = [&](int cx, int cy, int gx) {
         const int xl = (cx + ntl - 1) % ntl, yu = (cy + ntl - 1) % ntl;
         int total = run(yu * ntl + xl, 2, 3) + run(cy * ntl + xl, 1, 3);
         for (int j = 0; j < gx; ++j) total += run(yu * ntl + cx + j, 2, 4) + run(cy * ntl + cx + j, 0, 4);
         return total;
     };
-    for (int cy = 0; cy < ntl; ++cy) {
-        for (const auto& st0 : strips) {
-            // a strip too long for one item is cut back to single tiles: their
-            // partial sums are half as many, which shortens the reduction
-            std::vector<std::pair<int, int>> parts;
-            if (st0.second > 1 && strip_total(st0.first, cy, st0.second) > chunk) {
-                for (int j = 0; j < st0.second; ++j) parts.push_back({st0.first + j, 1});
-            } else {
-                parts.push_back(st0);
-            }
-            for (const auto& st : parts) {
-            const int cx = st.first, gx = st.second;
-            const int total = strip_total(cx, cy, gx);
-            if (total <= chunk) {
-                items.push_back({cx, cy, 0, total, -1, gx, 0, 0});
-            } else {
-                const int nch = (total + chunk - 1) / chunk;
-                splits.push_back({cx, cy, slots, nch});
-                for (int k = 0; k < nch; ++k)
-                    items.push_back({cx, cy, k * chunk, std::min(chunk, total - k * chunk), slots + k, gx, 0, 0});
-                slots += nch;
-            }
+    auto spread_items = [&](int chunk) {
+        items.clear();
+        splits.clear();
+        slots = 0;
+        for (int cy = 0; cy < ntl; ++cy) {
+            for (const auto& st0 : strips) {
+                // a strip too long for one item is cut back to single tiles: their
+                // partial sums are half as many, which shortens the reduction
+                std::vector<std::pair<int, int>> parts;
+                if (st0.second > 1 && strip_total(st0.first, cy, st0.second) > chunk) {
+                    for (int j = 0; j < st0.second; ++j) parts.push_back({st0.first + j, 1});
+                } else {
+                    parts.push_back(st0);
+                }
+                for (const auto& st : parts) {
+                    const int cx = st.first, gx = st.second;
+                    const int total = strip_total(cx, cy, gx);
+                    if (total <= chunk) {
+                        items.push_back({cx, cy, 0, total, -1, gx, 0, 0});
+                    } else {
+                        const int nch = (total + chunk - 1) / chunk;
+                        splits.push_back({cx, cy, slots, nch});
+                        for (int k = 0; k < nch; ++k)
+                            items.push_back({cx, cy, k * chunk, std::min(chunk, total - k * chunk), slots + k, gx, 0, 0});
+                        slots += nch;
+                    }
+                }
             }
         }
-    }
+    };
+    // Items of half the most visits (one visit per thread) where the launch lasts
+    // as long as its longest items and the added partial sums are few. Adjoint,
+    // items of 512 and of 256 visits: 128 rows, 180 views (75 partial sums)
+    // 20.5 and 17.5 us; 512 rows, 180 views, W = 8 28.2 and 25.1; 1024 and 180
+    // (1214 items) 36.7 and 35.8. Past the limits it gains little or loses: 1024
+    // and 720 (1545 sums) 42.9 and 46.0; 2048 and 180 (4350 items) 58.7 and 59.3.
+    const int half = rn::A2_NT;
+    if (p.a2_chunk > half) spread_items(half);
+    if (p.a2_chunk <= half || slots > cus || (int)items.size() > 6 * cus) spread_items(p.a2_chunk);
     // forward columns in order, without repeats
     std::vector<int> fcols;
     for (int cx = std::max(ntl / 2 - 1, 0); cx < ntl; ++cx) fcols.push_back(cx);
@@ -444,15 +462,8 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
     p.n_fitems = (int)fitems.size();
     p.items_h = items;
     p.fitems_h = fitems;
-    {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p.device) != hipSuccess || cus < 1) {
-            (void)hipGetLastError();
-            cus = 1;
-        }
-        p.f3_resident = std::max(1, rn::f3_blocks_per_cu(p.W, p.T) * cus);
-        p.f3_grid = std::max(1, std::min(p.n_fitems, p.f3_resident));
-    }
+    p.f3_resident = std::max(1, rn::f3_blocks_per_cu(p.W, p.T) * cus);
+    p.f3_grid = std::max(1, std::min(p.n_fitems, p.f3_resident));
     std::stable_sort(splits.begin(), splits.end(),
                      [](const rn::SplitTile& a, const rn::SplitTile& b) { return a.cx < b.cx; });
     std::vector<int> split_cols(ntl + 1, 0);
