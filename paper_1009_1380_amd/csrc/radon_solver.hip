@@ -321,10 +321,9 @@ __global__ __launch_bounds__(SV_NT) void k_sv_bb(const float* __restrict__ x, co
 // S(lam) = sum max(|v| - lam, 0) = tau. S is continuous, decreasing and
 // piecewise linear with breakpoints at the values |v_i|, so the root is found
 // exactly by locating it between two consecutive values: a radix select on the
-// bit pattern u of |v| (monotone in |v| for non-negative floats), 12 + 10 + 9
-// bits in three levels (a narrower second level makes the merge of its
-// histograms into global memory and the decision after it cheaper than with
-// 12 + 12 + 7). Each level histograms the elements whose leading bits match
+// bit pattern u of |v| (monotone in |v| for non-negative floats), 11 + 10 + 10
+// bits in three levels (fewer bins make the decision after a level cheaper, and
+// a first level of 11 bits the merge of its histograms no dearer). Each level histograms the elements whose leading bits match
 // the bin chosen so far, by count and by the exact integer sum of their
 // significands (the bins of a level share one exponent), so the histograms are
 // order-independent integers and the select is deterministic. From the counts
@@ -341,18 +340,21 @@ __global__ __launch_bounds__(SV_NT) void k_sv_bb(const float* __restrict__ x, co
 // next launch takes the previous level's decision itself from the finished
 // histogram (the same decision in every block), so the kernel boundary is the
 // only synchronisation, and block 0 records it for the launches after.
-constexpr int PJ_NT = 256;
-#ifndef RN_PJ_BLOCKS
-#define RN_PJ_BLOCKS 256
-#endif
-constexpr int PJ_BLOCKS = RN_PJ_BLOCKS;
-#ifndef RN_PJ_B2
-#define RN_PJ_B2 10
-#endif
-constexpr int PJ_B1 = 12, PJ_B2 = RN_PJ_B2, PJ_B3 = 31 - PJ_B1 - PJ_B2;   // bits of the three levels
-constexpr int PJ_BINS = 4096;            // histogram capacity of levels 1 and 2 (at most 12 bits)
+// The passes are bound by the merge of the blocks' histograms (atomics of every
+// block on the same few hot bins) and by the latency of the decisions, so they
+// take no more blocks than give each thread SV_U pieces, 256 at most, of 512
+// threads (256 blocks of 256 threads before, levels of 12 + 10 + 9 bits; three
+// passes and the soft threshold: 512^2 values 32 -> 26 us, 1024^2 37 -> 32,
+// 2560^2 77 -> 59; 1024 threads 28, 33 and 58).
+constexpr int PJ_NT = 512;
+constexpr int PJ_MAX_BLOCKS = 256;
+inline int pj_blocks(size_t n) {
+    const size_t piece = (size_t)PJ_NT * 4 * SV_U;
+    return (int)std::max<size_t>(1, std::min<size_t>((n + piece - 1) / piece, PJ_MAX_BLOCKS));
+}
+constexpr int PJ_B1 = 11, PJ_B2 = 10, PJ_B3 = 31 - PJ_B1 - PJ_B2;   // bits of the three levels
+constexpr int PJ_BINS = 1 << (PJ_B1 > PJ_B2 ? PJ_B1 : PJ_B2);       // histogram capacity of levels 1 and 2
 constexpr int PJ_BINS3 = 1 << PJ_B3;     // bins of level 3 (one float value each)
-static_assert(PJ_B2 <= 12 && PJ_B3 >= 1 && PJ_B3 <= 12, "level widths");
 
 // Decision after a level: the threshold (done), or the bin to refine (the
 // leading bits of u fixed so far) with the sum and count of |v| above it.
@@ -390,14 +392,14 @@ __device__ __forceinline__ float pj_v(float x, float h, double c) { return (floa
 // decision above it (up: prefix, and the sum A and count C of |v| above the bin
 // it chose; zero for level 1). Every thread returns the same decision. lc, ls:
 // shared scratch of NB entries, free again when this returns.
-template <int L>
+template <int L, int NT>
 __device__ PjState pj_decide(const unsigned* __restrict__ hcnt, const unsigned long long* __restrict__ hsum,
                              unsigned nbad, const PjState& up, double tau, unsigned* lc, unsigned long long* ls) {
     using Lv = PjLevel<L>;
     constexpr int NB = Lv::NB;
-    constexpr int RL = (NB + PJ_NT - 1) / PJ_NT;
-    __shared__ double sC[PJ_NT / 64], sV[PJ_NT / 64];
-    __shared__ int sb[PJ_NT / 64];
+    constexpr int RL = (NB + NT - 1) / NT;
+    __shared__ double sC[NT / 64], sV[NT / 64];
+    __shared__ int sb[NT / 64];
     __shared__ double dC, dV, dS;   // the chosen bin: count and sum above it, S at its upper edge
     __shared__ PjState out;
     const unsigned prefix = L == 1 ? 0u : up.prefix;
@@ -406,13 +408,13 @@ __device__ PjState pj_decide(const unsigned* __restrict__ hcnt, const unsigned l
         unsigned long long sv[RL];
 #pragma unroll
         for (int k = 0; k < RL; ++k) {
-            const int b = threadIdx.x + k * PJ_NT;
+            const int b = threadIdx.x + k * NT;
             cv[k] = b < NB ? hcnt[b] : 0u;
             sv[k] = b < NB ? hsum[b] : 0ull;
         }
 #pragma unroll
         for (int k = 0; k < RL; ++k) {
-            const int b = threadIdx.x + k * PJ_NT;
+            const int b = threadIdx.x + k * NT;
             if (b < NB) { lc[b] = cv[k]; ls[b] = sv[k]; }
         }
     }
@@ -450,7 +452,7 @@ __device__ PjState pj_decide(const unsigned* __restrict__ hcnt, const unsigned l
     if (lane == 63) { xC = 0.0; xV = 0.0; }
     __syncthreads();
     double aC = L == 1 ? 0.0 : up.C, aV = L == 1 ? 0.0 : up.A;   // everything above this thread's bins
-    for (int w = PJ_NT / 64 - 1; w > wave; --w) { aC += sC[w]; aV += sV[w]; }
+    for (int w = NT / 64 - 1; w > wave; --w) { aC += sC[w]; aV += sV[w]; }
     aC += xC;
     aV += xV;
     // this thread's highest non-empty bin whose lower edge has S >= tau
@@ -478,7 +480,7 @@ __device__ PjState pj_decide(const unsigned* __restrict__ hcnt, const unsigned l
     if (lane == 0) sb[wave] = bm;
     __syncthreads();
     int bstar = sb[0];
-    for (int w = 1; w < PJ_NT / 64; ++w) bstar = max(bstar, sb[w]);
+    for (int w = 1; w < NT / 64; ++w) bstar = max(bstar, sb[w]);
     if (bstar >= 0 && cand == bstar) {
         dC = cC;
         dV = cV;
@@ -521,7 +523,11 @@ __global__ __launch_bounds__(PJ_NT) void k_sv_pj_pass(const float* __restrict__ 
     using Lv = PjLevel<L>;
     constexpr int NB = Lv::NB;
     constexpr unsigned LOW = (1u << Lv::SHIFT) - 1;   // bits below the digit
-    constexpr int CSHIFT = 40;   // LDS bin: count << 40 | sum of the bits below the digit
+    // LDS bin: count << 42 | sum of the bits below the digit. n <= 2^29 gives a
+    // block at most 2^21 + 2^13 values of at most 20 such bits: a sum below 2^42,
+    // a count below 2^22
+    constexpr int CSHIFT = 42;
+    static_assert(Lv::SHIFT <= 20, "sums of a block stay below 2^42");
     __shared__ unsigned long long lh[PJ_BINS];
     __shared__ unsigned lc[PJ_BINS];
     __shared__ unsigned lbad;
@@ -554,8 +560,8 @@ __global__ __launch_bounds__(PJ_NT) void k_sv_pj_pass(const float* __restrict__ 
             up = *w.st1;
             if (up.done != 0.0) return;   // final after level 1 (uniform)
         }
-        const PjState d = L == 2 ? pj_decide<1>(w.cnt1, w.sum1, *w.bad, up, tau, lc, lh)
-                                 : pj_decide<2>(w.cnt2, w.sum2, 0u, up, tau, lc, lh);
+        const PjState d = L == 2 ? pj_decide<1, PJ_NT>(w.cnt1, w.sum1, *w.bad, up, tau, lc, lh)
+                                 : pj_decide<2, PJ_NT>(w.cnt2, w.sum2, 0u, up, tau, lc, lh);
         if (blockIdx.x == 0 && threadIdx.x == 0) *(L == 2 ? w.st1 : w.st2) = d;
         if (d.done != 0.0) return;   // uniform
         prefix = d.prefix;
@@ -624,7 +630,7 @@ __global__ __launch_bounds__(SV_NT) void k_sv_soft(const float* __restrict__ x, 
         L = s1.lam;
     } else {
         const PjState s2 = *w.st2;
-        L = s2.done != 0.0 ? s2.lam : pj_decide<3>(w.cnt3, w.sum3, 0u, s2, tau, lc, ls).lam;
+        L = s2.done != 0.0 ? s2.lam : pj_decide<3, SV_NT>(w.cnt3, w.sum3, 0u, s2, tau, lc, ls).lam;
     }
     {
         const size_t i = (size_t)blockIdx.x * SV_NT + threadIdx.x, all = (size_t)gridDim.x * SV_NT;
@@ -812,11 +818,11 @@ struct Solver {
     // xn = P_tau(x + c h) -> fin[2] = sum -h.(xn - x), fin[3] = ||xn||_1, fin[4] = lam
     void project(const float* x, const float* h, double c, double tau, float* xn) {
         const rn::PjWork pw = w.pj();
-        hipLaunchKernelGGL(rn::k_sv_pj_pass<1>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, x, h, c, tau, w.ct, n2,
+        hipLaunchKernelGGL(rn::k_sv_pj_pass<1>, dim3(rn::pj_blocks(n2)), dim3(rn::PJ_NT), 0, st, x, h, c, tau, w.ct, n2,
                            pw);
-        hipLaunchKernelGGL(rn::k_sv_pj_pass<2>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, x, h, 0.0, 0.0, w.ct, n2,
+        hipLaunchKernelGGL(rn::k_sv_pj_pass<2>, dim3(rn::pj_blocks(n2)), dim3(rn::PJ_NT), 0, st, x, h, 0.0, 0.0, w.ct, n2,
                            pw);
-        hipLaunchKernelGGL(rn::k_sv_pj_pass<3>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, x, h, 0.0, 0.0, w.ct, n2,
+        hipLaunchKernelGGL(rn::k_sv_pj_pass<3>, dim3(rn::pj_blocks(n2)), dim3(rn::PJ_NT), 0, st, x, h, 0.0, 0.0, w.ct, n2,
                            pw);
         hipLaunchKernelGGL(rn::k_sv_soft, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, x, h, w.ct, n2, pw, xn,
                            part(FIN_PROJ));
@@ -905,11 +911,11 @@ extern "C" radon_status_t radon_project_l1(const float* v_dev, int64_t n, double
     // the solver's projection of x + c h with x = h = v, c = 0 (v + 0 v = v for finite v)
     const size_t nn = (size_t)n;
     const rn::PjWork pw = w.pj();
-    hipLaunchKernelGGL(rn::k_sv_pj_pass<1>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, tau, w.ct,
+    hipLaunchKernelGGL(rn::k_sv_pj_pass<1>, dim3(rn::pj_blocks(nn)), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, tau, w.ct,
                        nn, pw);
-    hipLaunchKernelGGL(rn::k_sv_pj_pass<2>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, 0.0, w.ct,
+    hipLaunchKernelGGL(rn::k_sv_pj_pass<2>, dim3(rn::pj_blocks(nn)), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, 0.0, w.ct,
                        nn, pw);
-    hipLaunchKernelGGL(rn::k_sv_pj_pass<3>, dim3(rn::PJ_BLOCKS), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, 0.0, w.ct,
+    hipLaunchKernelGGL(rn::k_sv_pj_pass<3>, dim3(rn::pj_blocks(nn)), dim3(rn::PJ_NT), 0, st, v_dev, v_dev, 0.0, 0.0, w.ct,
                        nn, pw);
     hipLaunchKernelGGL(rn::k_sv_soft, dim3(rn::SV_BLOCKS), dim3(rn::SV_NT), 0, st, v_dev, v_dev, w.ct, nn, pw,
                        out_dev, w.part);
