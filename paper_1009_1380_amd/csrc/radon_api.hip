@@ -575,6 +575,7 @@ Work stack_work(const Plan& p, int slices) {
 radon_status_t api_fail(radon_status_t st, const char* msg) { return fail(st, "%s", msg); }
 radon_status_t api_ok() { return ok(); }
 radon_status_t api_check_plan(radon_plan_t plan) { return check_plan(plan); }
+int api_stack_slices(radon_plan_t plan, int batch, hipStream_t st) { return stack_slices(plan->p, batch, st); }
 radon_status_t api_run_forward(Plan& p, const float* img, float* sino, hipStream_t st) {
     return run_forward(p, plan_work(p), img, sino, st);
 }

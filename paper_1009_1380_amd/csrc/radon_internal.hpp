@@ -146,6 +146,8 @@ std::vector<double> ring_cubic_basis(int n_det);
 radon_status_t api_fail(radon_status_t st, const char* msg);
 radon_status_t api_ok();
 radon_status_t api_check_plan(radon_plan_t plan);
+// slices a batched call of `batch` takes per pass (allocates their workspace)
+int api_stack_slices(radon_plan_t plan, int batch, hipStream_t st);
 radon_status_t api_run_forward(Plan& p, const float* img, float* sino, hipStream_t st);
 radon_status_t api_run_adjoint(Plan& p, const float* sino, float* img, hipStream_t st);
 
