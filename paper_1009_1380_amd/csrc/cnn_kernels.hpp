@@ -94,8 +94,9 @@ __device__ __forceinline__ unsigned nonzero_bits(uint4 v) {
 
 // A piece with the channels whose bit of m is clear set to zero.
 __device__ __forceinline__ uint4 mask_piece(uint4 v, unsigned m) {
-    auto two = [&](unsigned b) { return ((b & 1u) ? 0xffffu : 0u) | ((b & 2u) ? 0xffff0000u : 0u); };
-    return make_uint4(v.x & two(m), v.y & two(m >> 2), v.z & two(m >> 4), v.w & two(m >> 6));
+    auto bit = [&](int k) { return (unsigned)((int)(m << (31 - k)) >> 31); };   // all ones where bit k is set
+    auto two = [&](int k) { return (bit(k) & 0xffffu) | (bit(k + 1) & 0xffff0000u); };
+    return make_uint4(v.x & two(0), v.y & two(2), v.z & two(4), v.w & two(6));
 }
 
 // ---------------------------------------------------------------- epilogues
@@ -456,8 +457,8 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(6))) vo
 // products. Blocks of 32 x 32 channels, for layers whose chunks are few, run
 // with one tap per wave: with three waves on a CU the products waited for each
 // other (1260 cycles per tile where the instructions take 770).
-// Measured at batch 8, 512 x 512: 64 -> 32 channels (77 GFLOP) 142 us, 128 -> 64
-// 116, 256 -> 128 116; 1191, 572 and 511 us with 2-byte operand reads and one
+// Measured at batch 8, 512 x 512: 64 -> 32 channels (77 GFLOP) 139 us, 128 -> 64
+// and 256 -> 128 113; 1191, 572 and 511 us with 2-byte operand reads and one
 // tile in flight, 169, 152 and 144 with the transposition in registers, whose
 // loads touched one cache line per lane.
 // Grid: x = chunks, y = blocks of CIB input channels, z = of COB output channels.
@@ -509,7 +510,7 @@ constexpr int WG_GS = 68, WG_XS = 100;
 constexpr int wgrad_threads(int cob, int cib, int tw) { return cob / 32 * (cib / 32) * (9 / tw) * 64; }
 
 template <int COB, int CIB, int TW, bool UP, int WD>
-__global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(WgradArgs a) {
+__global__ __launch_bounds__((wgrad_threads(COB, CIB, TW))) void k_conv3x3_wgrad(WgradArgs a) {
     constexpr int NT = wgrad_threads(COB, CIB, TW);
     constexpr int NG = COB / 8 * 64, NX = CIB / 8 * 100, RU = (NG + NX + NT - 1) / NT;
     constexpr int GP = COB / 8 * WG_GS, XP = CIB / 8 * WG_XS;   // pieces of a buffer
@@ -520,11 +521,12 @@ __global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(W
     constexpr int us = UP ? 1 : 0;
     const int Hi = a.H >> us, Wi = a.W >> us;
 
-    // this thread's pieces: place in LDS (-1: none), offset from the tile's first
-    // pixel (input: from one row and column before it), row and column in the tile
+    // this thread's pieces: place in LDS (-1: none), address in the first tile (input:
+    // one row and column before it), row and column in the tile
     int at[RU], row[RU], col[RU];
-    unsigned off[RU];
-    bool isg[RU], has[RU];
+    const uint4* p0[RU];
+    bool isg[RU];
+    unsigned has = 0u;                       // a bit per piece whose plane is there
 #pragma unroll
     for (int k = 0; k < RU; ++k) {
         const int e = tid + k * NT;
@@ -535,31 +537,51 @@ __global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(W
         col[k] = isg[k] ? r % 8 : r % 10 - 1;
         const int plane = (isg[k] ? cb : ib) / 8 + pl;
         at[k] = e < NG + NX ? (isg[k] ? pl * WG_GS + r : GP + pl * WG_XS + r) : -1;
-        has[k] = e < NG + NX && plane < (isg[k] ? a.Pg : a.Pi);
-        off[k] = !has[k] ? 0u : (unsigned)(isg[k] ? (plane * a.H + row[k]) * a.W + col[k]
-                                                  : (plane * Hi + (row[k] >> us) + 1) * Wi + (col[k] >> us) + 1);
+        const bool ok = e < NG + NX && plane < (isg[k] ? a.Pg : a.Pi);
+        has |= ok ? 1u << k : 0u;
+        p0[k] = isg[k] ? a.g + ((ptrdiff_t)plane * a.H + row[k]) * a.W + col[k]
+                       : a.in + ((ptrdiff_t)plane * Hi + (row[k] >> us)) * Wi + (col[k] >> us);
     }
+    // Requests are made without branches around them (a piece that is not there
+    // reads the tensor's first and is zeroed when it is stored): under branches the
+    // compiler cannot count the requests in flight, and every store would wait for
+    // all of them instead of its own tile's (64 x 64 blocks 119 us with branches, 113
+    // without; 32 x 32 blocks 69 and 61).
+    const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
+    TileAt cur = TileAt::of(t0, a.H, a.W);   // the next tile to request
     uint4 vr[WD][RU];
-    unsigned mr[WD][RU] = {};
-    auto load = [&](const TileAt& t, uint4 (&v)[RU], unsigned (&mk)[RU]) {
-        const ptrdiff_t gb = ((ptrdiff_t)t.b * a.Pg * a.H + t.y) * a.W + t.x;
-        const uint4* gp = a.g + gb;
-        const uint4* xp = a.in + (((ptrdiff_t)t.b * a.Pi * Hi + (t.y >> us) - 1) * Wi + (t.x >> us) - 1);
-        const bool inner = t.y > 0 && t.x > 0 && t.y + 8 < a.H && t.x + 8 < a.W;   // uniform
+    unsigned mr[WD][RU], live[WD];           // masks, a bit per piece that is there
+    const uint8_t* gmask = a.gmask ? a.gmask : reinterpret_cast<const uint8_t*>(a.g);
+    const unsigned nomask = a.gmask ? 0u : 255u;
+    auto load = [&](int t, uint4 (&v)[RU], unsigned (&mk)[RU], unsigned& there) {
+        const bool inner = t < t1 && cur.y > 0 && cur.x > 0 && cur.y + 8 < a.H && cur.x + 8 < a.W;   // uniform
+        const ptrdiff_t dg = ((ptrdiff_t)cur.b * a.Pg * a.H + cur.y) * a.W + cur.x;
+        const ptrdiff_t dx = ((ptrdiff_t)cur.b * a.Pi * Hi + (cur.y >> us)) * Wi + (cur.x >> us);
+        const uint4* p[RU];
+        there = has;
+        if (!inner) {
+#pragma unroll
+            for (int k = 0; k < RU; ++k)
+                if (!(t < t1 && (unsigned)(cur.y + row[k]) < (unsigned)a.H && (unsigned)(cur.x + col[k]) < (unsigned)a.W))
+                    there &= ~(1u << k);
+        }
+#pragma unroll
+        for (int k = 0; k < RU; ++k) p[k] = (there >> k & 1u) ? p0[k] + (isg[k] ? dg : dx) : a.g;
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
-            const int y = t.y + row[k], x = t.x + col[k];
-            v[k] = make_uint4(0u, 0u, 0u, 0u);
-            if (has[k] && (inner || (y >= 0 && y < a.H && x >= 0 && x < a.W))) {
-                v[k] = (isg[k] ? gp : xp)[off[k]];
-                if (a.gmask && isg[k]) mk[k] = a.gmask[gb + off[k]];
-            }
+            v[k] = *p[k];
+            if (k * NT < NG) mk[k] = isg[k] ? gmask[p[k] - a.g] : 0u;
         }
+        cur.next(a.H, a.W);
     };
-    auto store = [&](uint4* buf, const uint4 (&v)[RU], const unsigned (&mk)[RU]) {
+    auto store = [&](uint4* buf, const uint4 (&v)[RU], const unsigned (&mk)[RU], unsigned there) {
 #pragma unroll
-        for (int k = 0; k < RU; ++k)
-            if (at[k] >= 0) buf[at[k]] = a.gmask && isg[k] ? mask_piece(v[k], mk[k]) : v[k];
+        for (int k = 0; k < RU; ++k) {
+            const unsigned ok = (unsigned)((int)(there << (31 - k)) >> 31);   // all ones where it is there
+            uint4 q = make_uint4(v[k].x & ok, v[k].y & ok, v[k].z & ok, v[k].w & ok);
+            if (k * NT < NG) q = mask_piece(q, mk[k] | (isg[k] ? nomask : 255u));
+            if (at[k] >= 0) buf[at[k]] = q;
+        }
     };
 
     const int i = lane & 31, kh = lane >> 5;
@@ -569,25 +591,16 @@ __global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(W
     const int go = wm * 4 * WG_GS * 16 + tr_at(lane, WG_GS * 16);
     const int xo = (GP + wn * 4 * WG_XS + dy * 10 + dx) * 16 + tr_at(lane, WG_XS * 16);
     f32x16 acc[TW] = {};
-    const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
-    TileAt cur = TileAt::of(t0, a.H, a.W);   // the next tile to load
 #pragma unroll
-    for (int d = 0; d < WD; ++d)
-        if (t0 + d < t1) {
-            load(cur, vr[d], mr[d]);
-            cur.next(a.H, a.W);
-        }
-    store(sh[0], vr[0], mr[0]);
+    for (int d = 0; d < WD; ++d) load(t0 + d, vr[d], mr[d], live[d]);
+    store(sh[0], vr[0], mr[0], live[0]);
     lds_sync();
     for (int tb = t0; tb < t1; tb += WD) {
 #pragma unroll
         for (int d = 0; d < WD; ++d) {   // slot d of the ring held tile t = tb + d, which is in LDS
             const int t = tb + d;
             if (t >= t1) break;   // uniform
-            if (t + WD < t1) {
-                load(cur, vr[d], mr[d]);
-                cur.next(a.H, a.W);
-            }
+            load(t + WD, vr[d], mr[d], live[d]);
             const char* buf = reinterpret_cast<const char*>(sh[(t - t0) & 1]);
             uint2 ga[8], gx[7 + TW];
 #pragma unroll
@@ -599,7 +612,7 @@ __global__ __launch_bounds__(wgrad_threads(COB, CIB, TW)) void k_conv3x3_wgrad(W
             for (int r = 0; r < 8; ++r)
 #pragma unroll
                 for (int y = 0; y < TW; ++y) acc[y] = mfma(ga[r].x, ga[r].y, gx[r + y].x, gx[r + y].y, acc[y]);
-            if (t + 1 < t1) store(sh[(t + 1 - t0) & 1], vr[(d + 1) % WD], mr[(d + 1) % WD]);
+            store(sh[(t + 1 - t0) & 1], vr[(d + 1) % WD], mr[(d + 1) % WD], live[(d + 1) % WD]);
             lds_sync();
         }
     }
