@@ -92,6 +92,14 @@ __device__ __forceinline__ unsigned nonzero_bits(uint4 v) {
     return (m | m >> 15) & 0xffu;
 }
 
+// A piece loaded as one vector (assigning the struct itself into an array of them
+// makes the compiler keep the array in LDS).
+__device__ __forceinline__ uint4 ld_piece(const uint4* p) {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // A piece with the channels whose bit of m is clear set to zero.
 __device__ __forceinline__ uint4 mask_piece(uint4 v, unsigned m) {
     auto bit = [&](int k) { return (unsigned)((int)(m << (31 - k)) >> 31); };   // all ones where bit k is set
@@ -130,8 +138,9 @@ struct Epilogue {
 // skip of EPI_ACT, the residual of EPI_ONE. Requested for all of a wave's blocks
 // (EPI_POOLG: for the next one) before the first is worked on, without branches
 // per lane (lanes outside the image read the first piece and store nothing), and
-// with the biases in LDS: one memory latency instead of one per piece (batch 8, 512 x 512: 64 -> 32 channels
-// with its skip 163 -> 155 us, the pooled gradient 64 -> 32 channels 89 -> 77).
+// with the biases in LDS: one memory latency instead of one per piece (batch 8,
+// 512 x 512: 64 -> 32 channels with its skip 163 -> 155 us, the pooled gradient
+// 64 -> 32 channels 89 -> 77).
 template <int EPI>
 struct EpiIn {
     uint4 s[2][EPI == EPI_POOLG ? 4 : 1];
@@ -326,18 +335,23 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(CB == 3
     const int Hi = UP ? a.H / 2 : a.H, Wi = UP ? a.W / 2 : a.W, HWi = Hi * Wi;
     const int wy0 = (UP ? ty0 / 2 : ty0) - 1, wx0 = (UP ? tx0 / 2 : tx0) - 1;
 
-    // this thread's pieces of a chunk: their place in the first chunk, -1 for zero
+    // this thread's pieces of a chunk: their place in the first chunk, and for the
+    // window whether they lie in the image (all ones) or not: those outside read
+    // the first piece, without a branch, and are zeroed when they are stored
     int xo[RX], ao[RA];
+    unsigned in[RX];
 #pragma unroll
     for (int k = 0; k < RX; ++k) {
         const int e = tid + k * CONV_NT;
         const int pl = e / WIN, r = e - pl * WIN, y = wy0 + r / WX, x = wx0 + r % WX;
-        xo[k] = (e < NX && y >= 0 && y < Hi && x >= 0 && x < Wi) ? pl * HWi + y * Wi + x : -1;
+        const bool ok = e < NX && y >= 0 && y < Hi && x >= 0 && x < Wi;
+        xo[k] = ok ? pl * HWi + y * Wi + x : 0;
+        in[k] = ok ? ~0u : 0u;
     }
 #pragma unroll
     for (int k = 0; k < RA; ++k) {
         const int e = tid + k * CONV_NT;
-        ao[k] = e < NA ? (e / CB) * a.CoutP + cb + e % CB : -1;
+        ao[k] = e < NA ? (e / CB) * a.CoutP + cb + e % CB : 0;
     }
     if (ep.bias && tid < (EPI == EPI_ACT ? CB : EPI == EPI_ONE ? 1 : 0)) sb[tid] = ep.bias[cb + tid];
     const size_t img = (size_t)b * a.Pin * HWi;
@@ -347,22 +361,21 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(CB == 3
         const uint4* px = a.in + img + (size_t)(2 * c) * HWi;
         const uint4* pa = a.w + (size_t)c * 18 * a.CoutP;
 #pragma unroll
-        for (int k = 0; k < RX; ++k) {
-            vx[k] = make_uint4(0u, 0u, 0u, 0u);
-            if (xo[k] >= 0) {
-                vx[k] = px[xo[k]];
-                if (a.mask) vm[k] = a.mask[img + (size_t)(2 * c) * HWi + xo[k]];
-            }
-        }
+        for (int k = 0; k < RX; ++k) vx[k] = ld_piece(px + xo[k]);
 #pragma unroll
-        for (int k = 0; k < RA; ++k)
-            va[k] = ao[k] >= 0 ? pa[ao[k]] : make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < RA; ++k) va[k] = ld_piece(pa + ao[k]);
+        if (a.mask) {
+            const uint8_t* pm = a.mask + img + (size_t)(2 * c) * HWi;
+#pragma unroll
+            for (int k = 0; k < RX; ++k) vm[k] = pm[xo[k]];
+        }
     };
     auto store = [&](int s) {
 #pragma unroll
         for (int k = 0; k < RX; ++k) {
             const int e = tid + k * CONV_NT;
-            if (e < NX) sx[s][e] = a.mask ? mask_piece(vx[k], vm[k]) : vx[k];
+            const uint4 v = make_uint4(vx[k].x & in[k], vx[k].y & in[k], vx[k].z & in[k], vx[k].w & in[k]);
+            if (e < NX) sx[s][e] = a.mask ? mask_piece(v, vm[k]) : v;
         }
 #pragma unroll
         for (int k = 0; k < RA; ++k)
@@ -432,9 +445,9 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(CB == 3
     }
     // the wave's blocks m, n in order
     constexpr int NB = MW * NW;
-    EpiIn<EPI> in[NB];
+    EpiIn<EPI> ein[NB];
     auto ask = [&](int k) {
-        epilogue_load<EPI>(in[k], ep, b, a.CoutP / 8, (cb + (wm * MW + k / NW) * 32) / 8, ty0 + py + 2 * (k % NW), tx0 + px,
+        epilogue_load<EPI>(ein[k], ep, b, a.CoutP / 8, (cb + (wm * MW + k / NW) * 32) / 8, ty0 + py + 2 * (k % NW), tx0 + px,
                            a.H, a.W, kh);
     };
 #pragma unroll
@@ -442,7 +455,7 @@ __global__ __launch_bounds__(CONV_NT) __attribute__((amdgpu_waves_per_eu(CB == 3
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
         if (EPI == EPI_POOLG && k + 1 < NB) ask(k + 1);
-        epilogue<EPI>(ep, in[k], sb + (wm * MW + k / NW) * 32, acc[k / NW][k % NW], b, a.CoutP / 8,
+        epilogue<EPI>(ep, ein[k], sb + (wm * MW + k / NW) * 32, acc[k / NW][k % NW], b, a.CoutP / 8,
                       (cb + (wm * MW + k / NW) * 32) / 8, ty0 + py + 2 * (k % NW), tx0 + px, a.H, a.W, i, kh);
     }
 }
