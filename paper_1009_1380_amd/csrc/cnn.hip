@@ -197,9 +197,12 @@ size_t wgrad_chunks(long long B, int h, int w) {
 }
 size_t bias_chunks(long long B, int h, int w) { return (size_t)((B * h * w + cnn::BG_CHUNK - 1) / cnn::BG_CHUNK); }
 
+constexpr int CUS = 256;          // of a gfx950 device
 constexpr int WGRAD_FLIGHT = 2;   // tiles in flight (1 and 3 are no faster; 3 costs registers)
 template <int COB, int CIB, int TW, int WD = WGRAD_FLIGHT>
-void wgrad_go(const cnn::WgradArgs& a, int chunks, bool up, hipStream_t st) {
+void wgrad_go(cnn::WgradArgs a, int chunk0, int chunks, bool up, hipStream_t st) {
+    if (chunks <= 0) return;
+    a.chunk0 = chunk0;
     const dim3 grid((unsigned)chunks, (unsigned)cdiv(a.Cin, CIB), (unsigned)cdiv(a.Cout, COB));
     constexpr int NT = cnn::wgrad_threads(COB, CIB, TW);
     if (up) hipLaunchKernelGGL((cnn::k_conv3x3_wgrad<COB, CIB, TW, true, WD>), grid, dim3(NT), 0, st, a);
@@ -223,11 +226,23 @@ void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* g, const uint8_t* gmask
         const cnn::WgradArgs a{gp, gmask, reinterpret_cast<const uint4*>(in), pad_to(L.cout, 16) / 8, pad_to(L.cin, 16) / 8,
                                c.B, h, w, L.cout, L.cin, c.part};
         // 64 x 64 channels per workgroup read each tile the fewest times; smaller
-        // blocks where those would leave CUs without a workgroup
-        if (L.cout % 64 == 0 && L.cin % 64 == 0 && chunks * (L.cout / 64) * (L.cin / 64) >= 256)
-            wgrad_go<64, 64, 3>(a, (int)chunks, up, st);
-        else if (L.cin % 64 == 0 && chunks * cdiv(L.cout, 32) * (L.cin / 64) >= 256) wgrad_go<32, 64, 3>(a, (int)chunks, up, st);
-        else wgrad_go<32, 32, 1>(a, (int)chunks, up, st);
+        // blocks where those would leave CUs without a workgroup. A CU holds one
+        // such workgroup, so a last round that fills at most half of the CUs goes
+        // to smaller blocks in a launch of its own (264 workgroups, 8 images of 504 x
+        // 520: 208 us in one launch, 118 + 57 in two; above half the smaller blocks
+        // take as long as the round).
+        const int n = (int)chunks, m = (L.cout / 64) * (L.cin / 64);
+        if (L.cout % 64 == 0 && L.cin % 64 == 0 && n * m >= CUS) {
+            const int left = n - n * m / CUS * CUS / m;   // chunks of the last round
+            const int tail = left * m <= CUS / 2 ? left : 0;
+            wgrad_go<64, 64, 3>(a, 0, n - tail, up, st);
+            if (tail * m <= CUS / 4) wgrad_go<32, 32, 1>(a, n - tail, tail, up, st);
+            else wgrad_go<32, 64, 3>(a, n - tail, tail, up, st);
+        } else if (L.cin % 64 == 0 && n * cdiv(L.cout, 32) * (L.cin / 64) >= CUS) {
+            wgrad_go<32, 64, 3>(a, 0, n, up, st);
+        } else {
+            wgrad_go<32, 32, 1>(a, 0, n, up, st);
+        }
     }
     if (L.cin == 32 && L.cout == 1) {
         hipLaunchKernelGGL(cnn::k_bias_grad1, dim3((unsigned)bchunks), dim3(256), 0, st, g, (long long)c.B * h * w, h * w,

@@ -566,6 +566,7 @@ struct WgradArgs {
     const uint4* in;         // input pieces, Pi planes, H x W (UP: H/2 x W/2)
     int Pg, Pi, B, H, W, Cout, Cin;
     float* part;
+    int chunk0;              // the launch's first chunk
 };
 
 // Pieces of a staged plane: 8 x 8 of the gradient, 10 x 10 of the input; the
@@ -614,7 +615,7 @@ __global__ __launch_bounds__((wgrad_threads(COB, CIB, TW))) void k_conv3x3_wgrad
     // compiler cannot count the requests in flight, and every store would wait for
     // all of them instead of its own tile's (64 x 64 blocks 119 us with branches, 113
     // without; 32 x 32 blocks 69 and 61).
-    const int t0 = blockIdx.x * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
+    const int chunk = a.chunk0 + blockIdx.x, t0 = chunk * WG_TILES, t1 = min(t0 + WG_TILES, ntiles);
     TileAt cur = TileAt::of(t0, a.H, a.W);   // the next tile to request
     uint4 vr[WD][RU];
     unsigned mr[WD][RU], live[WD];           // masks, a bit per piece that is there
@@ -686,7 +687,7 @@ __global__ __launch_bounds__((wgrad_threads(COB, CIB, TW))) void k_conv3x3_wgrad
     const int ci = ib + wn * 32 + i;
 #pragma unroll
     for (int y = 0; y < TW; ++y) {
-        float* dst = a.part + ((size_t)blockIdx.x * 9 + 3 * (y + dy) + dx) * a.Cout * a.Cin;
+        float* dst = a.part + ((size_t)chunk * 9 + 3 * (y + dy) + dx) * a.Cout * a.Cin;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int co = cb + wm * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
