@@ -161,7 +161,8 @@ radon_status_t radon_adjoint_batched(radon_plan_t plan, int batch, const float* 
  * width, tile size) for the gridding, whose items from every slice are
  * drained longest first. The first call for a given set of device pointers
  * records these launches into one HIP graph (the launches of different
- * lengths on up to `n_branches` parallel branches, 1..16); later calls with
+ * lengths on up to `n_branches` parallel branches, 1..16, and on one or two
+ * where the slices are few and small and more are slower); later calls with
  * the same pointers replay it with one graph launch on `stream`. New pointers
  * record a new graph. Every slice's result equals its per-slice call bit for
  * bit. imgs_dev[i] is plan i's n*n image, sinos_dev[i] its n_views*n_det

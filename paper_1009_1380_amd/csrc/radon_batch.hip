@@ -349,7 +349,21 @@ radon_status_t radon_batch_create(radon_batch_t* out, int count, const radon_pla
     if (!b) return errf(RADON_ERR_OOM, "host allocation failed");
     b->device = dev;
     b->plans = ps;
-    const int nb = std::min(n_branches, count);
+    // Branches share the device's queues: a fork and a join cost some 10 us each, and
+    // more of them with more branches, while what they hide is the tail of one
+    // length's launches behind another's. So one branch for batches of few pixels
+    // and lengths, two up to eight million pixels. Forward and adjoint with 1, 2 and
+    // 4 branches: 1.6 million pixels of 2 sides 129, 162, 162 us; 2.4 of 3 199, 201,
+    // 235; 2.6 of 6 285, 272, 305; 5.1 of 4 279, 273, 295; 7.7 of 6 414, 373, 370;
+    // ten slices of 8 sides up to 2560 654, 579, 554; 42 million of 8 1445, 1334, 1320.
+    double pixels = 0;
+    std::vector<int> sides;
+    for (const radon_plan_t p : ps) {
+        pixels += (double)p->p.n * p->p.n;
+        if (std::find(sides.begin(), sides.end(), p->p.n) == sides.end()) sides.push_back(p->p.n);
+    }
+    const int most = pixels >= 8e6 ? 16 : pixels < 4.5e6 && sides.size() <= 5 ? 1 : 2;
+    const int nb = std::min({n_branches, count, most});
     for (int i = 0; i < nb; ++i) {
         hipStream_t s = nullptr;
         if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) {
