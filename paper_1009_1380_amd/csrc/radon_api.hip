@@ -252,7 +252,10 @@ radon_status_t run_adjoint(Plan& p, const rn::Work& w, const float* sino, float*
 // 180 views: forward and adjoint 436 us one by one, 100 together. One at a time
 // under profiling (a
 // stage time is one slice's), or where the workspace cannot be had: no memory,
-// or the stream is being captured, which forbids the allocation.
+// or the stream is being captured, which forbids the allocation. A capture of
+// another stream in global mode would refuse the allocation and be lost by it, so
+// this thread is in relaxed mode meanwhile: the stream being captured does not
+// use the new memory.
 int stack_slices(Plan& p, int batch, hipStream_t st) {
     if (batch < 2 || p.profiling || p.stack == 1) return 1;
     if (p.stack == 0) {
@@ -271,7 +274,14 @@ int stack_slices(Plan& p, int batch, hipStream_t st) {
         void* base = nullptr;
         size_t bytes = 0;
         for (size_t c : counts) bytes += (c * sizeof(float2) * slices + 255) / 256 * 256;
-        if (hipMalloc(&base, bytes) != hipSuccess) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+            (void)hipGetLastError();
+            return 1;
+        }
+        const hipError_t e = hipMalloc(&base, bytes);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
             (void)hipGetLastError();
             p.stack = 1;
             return 1;
