@@ -73,9 +73,11 @@ typedef enum {
  * allocates its workspace. It synchronises the device before returning.
  * On failure *out is set to NULL and nothing stays allocated. Release with
  * radon_plan_destroy.
- * Test hook: with the environment variable RADON_TEST_FAIL_ALLOC=k, the k-th
- * device allocation made while building a plan (counting from 1) fails as if
- * the device were out of memory (RADON_ERR_OOM).
+ * Test hook: with the environment variable RADON_TEST_FAIL_ALLOC=k set while a
+ * plan is built, the k-th device allocation made for it (counting from 1) fails
+ * as if the device were out of memory: RADON_ERR_OOM while building; the one
+ * after those is the workspace of the batched calls, which then go slice by
+ * slice.
  */
 radon_status_t radon_plan(radon_plan_t* out, int n, const double* angles, int n_views,
                           int n_det, double sigma, int W);
@@ -145,7 +147,9 @@ radon_status_t radon_fbp(radon_plan_t plan, const float* sino_dev, float* img_de
  * sinos_dev is batch*n_views*n_det float32. Slices small enough to leave the
  * device idle are taken several per pass; the workspace for that (at most 128
  * MiB) is allocated by the first call that uses it and freed with the plan.
- * Every slice's result equals its single call's bit for bit. */
+ * While it cannot be had (no memory, or `stream` is being captured), the slices
+ * go one by one, and the next call asks again. Every slice's result equals its
+ * single call's bit for bit. */
 radon_status_t radon_forward_batched(radon_plan_t plan, int batch, const float* imgs_dev,
                                      float* sinos_dev, void* stream);
 radon_status_t radon_adjoint_batched(radon_plan_t plan, int batch, const float* sinos_dev,

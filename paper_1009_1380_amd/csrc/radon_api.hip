@@ -116,8 +116,9 @@ std::vector<float> ramp_weights(int n_views, int N) {
 bool is_supported_length(int len) { return rn::length_supported(len); }
 
 // Failure-injection hook for the tests: with RADON_TEST_FAIL_ALLOC=k in the
-// environment, the k-th device allocation made while building a plan
-// (counting from 1) fails as if the device were out of memory.
+// environment while a plan is built, the k-th device allocation made for it
+// (counting from 1; the batched calls' workspace follows those of the building)
+// fails as if the device were out of memory.
 int test_fail_alloc_at() {
     const char* e = getenv("RADON_TEST_FAIL_ALLOC");
     return e ? atoi(e) : 0;
@@ -279,11 +280,10 @@ int stack_slices(Plan& p, int batch, hipStream_t st) {
             (void)hipGetLastError();
             return 1;
         }
-        const hipError_t e = hipMalloc(&base, bytes);
+        const hipError_t e = plan_malloc(p, &base, bytes);
         (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (e != hipSuccess) {
+        if (e != hipSuccess) {   // asked for again by the next call: memory may be free then
             (void)hipGetLastError();
-            p.stack = 1;
             return 1;
         }
         p.allocs.push_back(base);
@@ -557,6 +557,7 @@ radon_status_t build_plan(Plan& p, int n, const double* angles, int n_views, int
     if ((s = dev_alloc(p, &p.grid, (size_t)(n + 1) * G))) return s;
     if ((s = dev_alloc(p, &p.Yh, (size_t)n_views * (n_det / 2 + 1)))) return s;
     if ((s = dev_alloc(p, &p.Xr, (size_t)n_views * (n_det / 2 + 1)))) return s;
+    p.allocs.reserve(p.allocs.size() + 1);   // stack_slices, in a call that may not throw, adds one
     if (hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError();
         return fail(RADON_ERR_DEVICE, "device synchronisation failed after plan setup");
