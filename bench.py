@@ -286,7 +286,7 @@ def batch_times(dev, n_slices: int = 64, repeats: int = 5, seed: int = 0, tune: 
     plans = [Plan(n, uniform_angles(v), n, tuning=tuned[(n, v)][0]) for n, v in shapes]
     ms_slice_t, ms_graph_t = run_modes(plans)
     del plans
-    changed = sum(1 for k, (best, _, _) in tuned.items() if best != {"tile": 32, "a2_chunk": 512, "f3_chunk": 2048})
+    changed = sum(1 for (n, v), (best, _, _) in tuned.items() if best != Plan(n, uniform_angles(v), n).tuning())
 
     out.update({
         "per_slice_calls_autotuned": {"ms_per_step": round(ms_slice_t, 3), "Gsamples_per_s": gs(ms_slice_t)},

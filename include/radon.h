@@ -87,7 +87,8 @@ radon_status_t radon_plan(radon_plan_t* out, int n, const double* angles, int n_
  * the bins that balance the gridding work, read as uniform tiles):
  *   tile      side T of the square bins: 8, 16 or 32 with T dividing G/2 and
  *             T >= W; 0 = the largest that fits.
- *   a2_chunk  most visits in one spreading work item, 64..512; 0 = 512.
+ *   a2_chunk  most visits in one spreading work item, 64..512; 0 = 512, or 256
+ *             in small plans that run faster with it.
  *   f3_chunk  most samples in one forward-interpolation work item,
  *             256..65536; 0 = 2048.
  * Results do not depend on the choice beyond float32 rounding.

@@ -360,7 +360,7 @@ radon_status_t sort_samples(Plan& p, std::vector<int>& offsets_host) {
 // columns ntl/2-1, .., ntl-1, 0 are taken in consecutive pairs (the last pair
 // wraps to column 0) and the rows in pairs; each 2 x 2 super-tile's samples
 // are cut into items of at most kF3Chunk.
-radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
+radon_status_t build_work(Plan& p, const std::vector<int>& o4, bool a2_default) {
     const int ntl = p.ntl;
     auto run = [&](int bin, int c0, int c1) { return o4[4 * bin + c1] - o4[4 * bin + c0]; };
     std::vector<rn::TileItem> items;
@@ -369,7 +369,7 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
     std::vector<std::pair<int, int>> strips;   // (first column, columns)
     for (int cx = std::max(ntl / 2, 1); cx < ntl; cx += rn::A2_GX) strips.push_back({cx, std::min(rn::A2_GX, ntl - cx)});
     strips.push_back({0, 1});
-    int slots = 0;
+    int slots = 0, longest = 0;   // partial sums; most visits of a strip
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p.device) != hipSuccess || cus < 1) {
         (void)hipGetLastError();
@@ -390,6 +390,7 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
                 // a strip too long for one item is cut back to single tiles: their
                 // partial sums are half as many, which shortens the reduction
                 std::vector<std::pair<int, int>> parts;
+                longest = std::max(longest, strip_total(st0.first, cy, st0.second));
                 if (st0.second > 1 && strip_total(st0.first, cy, st0.second) > chunk) {
                     for (int j = 0; j < st0.second; ++j) parts.push_back({st0.first + j, 1});
                 } else {
@@ -411,15 +412,20 @@ radon_status_t build_work(Plan& p, const std::vector<int>& o4) {
             }
         }
     };
-    // Items of half the most visits (one visit per thread) where the launch lasts
-    // as long as its longest items and the added partial sums are few. Adjoint,
-    // items of 512 and of 256 visits: 128 rows, 180 views (75 partial sums)
+    spread_items(p.a2_chunk);
+    // By default, items of half the most visits (one visit per thread) where the
+    // launch lasts as long as its longest items and the added partial sums are few.
+    // Adjoint, items of 512 and of 256 visits: 128 rows, 180 views (75 partial sums)
     // 20.5 and 17.5 us; 512 rows, 180 views, W = 8 28.2 and 25.1; 1024 and 180
     // (1214 items) 36.7 and 35.8. Past the limits it gains little or loses: 1024
     // and 720 (1545 sums) 42.9 and 46.0; 2048 and 180 (4350 items) 58.7 and 59.3.
+    // Where no strip has more visits than that, both are the same items.
     const int half = rn::A2_NT;
-    if (p.a2_chunk > half) spread_items(half);
-    if (p.a2_chunk <= half || slots > cus || (int)items.size() > 6 * cus) spread_items(p.a2_chunk);
+    if (a2_default && longest > half) {
+        spread_items(half);
+        if (slots <= cus && (int)items.size() <= 6 * cus) p.a2_chunk = half;
+        else spread_items(p.a2_chunk);
+    }
     // forward columns in order, without repeats
     std::vector<int> fcols;
     for (int cx = std::max(ntl / 2 - 1, 0); cx < ntl; ++cx) fcols.push_back(cx);
@@ -552,7 +558,7 @@ radon_status_t build_plan(Plan& p, int n, const double* angles, int n_views, int
     if ((s = dev_alloc(p, &p.offs4, (size_t)4 * p.n_bins + 1))) return s;
     std::vector<int> offs;
     if ((s = sort_samples(p, offs))) return s;
-    if ((s = build_work(p, offs))) return s;
+    if ((s = build_work(p, offs, tuning.a2_chunk == 0))) return s;
     if ((s = dev_alloc(p, &p.T1, (size_t)(n + 1) * n))) return s;
     if ((s = dev_alloc(p, &p.grid, (size_t)(n + 1) * G))) return s;
     if ((s = dev_alloc(p, &p.Yh, (size_t)n_views * (n_det / 2 + 1)))) return s;
