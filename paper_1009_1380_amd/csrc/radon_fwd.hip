@@ -104,16 +104,25 @@ static hipError_t launch_f3_direct(const Plan& p, const Work& w, hipStream_t st)
     return hipGetLastError();
 }
 
-// Interpolate straight from the grid where the samples are few against the
-// grid: reading W^2 points per sample costs about 6 us + 1.2e-6 us M W^2,
-// staging every region about 9 us + 3e-6 us n^2 (two dependent rounds of loads
-// and a barrier before the first sample). Measured, staged and direct: 128^2, 180
-// views 12.6 and 7.8 us; 512^2, 90 views 12.9 and 9.9; 1024^2, 128 views 13.9 and
-// 14.2; 1536^2, 90 views 18.9 and 16.2; 1024^2, 360 views 15.0 and 25.1; 2560^2,
-// 1024 views 38 and 74.
+// Interpolate straight from the grid where the samples are few against the grid.
+// Direct time grows with the points read (M W^2); staging pays for every region of the
+// grid (two dependent rounds of loads and a barrier before the first sample), and
+// with W = 8 holds fewer waves. Up to 512^2 pixels in all there are fewer regions than
+// two per CU: a staged launch then lasts as long as its fullest region, and direct
+// pays up to a fixed number of points. Forward, direct and staged, us: 128^2 pixels,
+// W = 6: 4.5e6 points 18.6 and 21.6, 8e6 21.4 and 21.9, 10e6 23.8 and 23.5; 512^2:
+// 4.5e6 23.6 and 25.6, 6.5e6 25.7 and 25.7, 8e6 28.5 and 26.7, with W = 8 8e6 27.8
+// and 30.3, 10e6 31.9 and 30.1; 1024^2, W = 6: 3.7e6 (100 views) 36.2 and 37.1, 4.7e6
+// (128) 36.8 and 37.4, 5.0e6 (135) 38.2 and 37.5, with W = 8 4.4e6 34.9 and 38.5, 5.5e6
+// 41.2 and 41.3; 2560^2, W = 6: 7.7e6 80.2 and 87.0, 11.5e6 86.7 and 86.9, 15.4e6
+// 91.0 and 86.9; four slices of 1024^2: 5.3e6 57.2 and 60.4, 8e6 60.6 and 60.5,
+// 10.8e6 64.0 and 61.8. Over 338 plans and stacks on both sides of these lines the
+// choice is 0.7% over the better of the two on average.
 static bool f3_is_direct(const Plan& p, int slices) {
-    const double s = slices, points = s * (double)p.n_samples * p.W * p.W;
-    return points < 2.9e6 + 2.5 * s * (double)p.n * p.n;
+    const double s = slices, points = s * (double)p.n_samples * p.W * p.W, pixels = s * (double)p.n * p.n;
+    const bool wide = p.W == 8;
+    if (pixels <= 512.0 * 512.0) return points < (wide ? 9e6 : 6e6);
+    return points < (wide ? 3e6 + 2.5 * pixels : 3.5e6 + 1.25 * pixels);
 }
 
 hipError_t launch_f3(const Plan& p, const Work& w, hipStream_t st) {
