@@ -76,6 +76,7 @@ constexpr int NCONV = 8;
 
 struct radon_cnn_s {
     int device = 0;
+    int cus = 1;             // compute units of the device
     int B = 0, H = 0, W = 0;
     int step = 0;
     Conv conv[NCONV];
@@ -113,6 +114,13 @@ struct radon_cnn_s {
         return true;
     }
     void chk(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
+    bool find_device() {
+        if (hipGetDevice(&device) == hipSuccess &&
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
+            return true;
+        (void)hipGetLastError();
+        return false;
+    }
 };
 
 namespace {
@@ -197,7 +205,6 @@ size_t wgrad_chunks(long long B, int h, int w) {
 }
 size_t bias_chunks(long long B, int h, int w) { return (size_t)((B * h * w + cnn::BG_CHUNK - 1) / cnn::BG_CHUNK); }
 
-constexpr int CUS = 256;          // of a gfx950 device
 constexpr int WGRAD_FLIGHT = 2;   // tiles in flight (1 and 3 are no faster; 3 costs registers)
 template <int COB, int CIB, int TW, int WD = WGRAD_FLIGHT>
 void wgrad_go(cnn::WgradArgs a, int chunk0, int chunks, bool up, hipStream_t st) {
@@ -231,14 +238,14 @@ void conv_wgrad(radon_cnn_s& c, Conv& L, const uint16_t* g, const uint8_t* gmask
         // to smaller blocks in a launch of its own (264 workgroups, 8 images of 504 x
         // 520: 208 us in one launch, 118 + 57 in two; above half the smaller blocks
         // take as long as the round).
-        const int n = (int)chunks, m = (L.cout / 64) * (L.cin / 64);
-        if (L.cout % 64 == 0 && L.cin % 64 == 0 && n * m >= CUS) {
-            const int left = n - n * m / CUS * CUS / m;   // chunks of the last round
-            const int tail = left * m <= CUS / 2 ? left : 0;
+        const int n = (int)chunks, m = (L.cout / 64) * (L.cin / 64), cus = c.cus;
+        if (L.cout % 64 == 0 && L.cin % 64 == 0 && n * m >= cus) {
+            const int left = n - n * m / cus * cus / m;   // chunks of the last round
+            const int tail = left * m <= cus / 2 ? left : 0;
             wgrad_go<64, 64, 3>(a, 0, n - tail, up, st);
-            if (tail * m <= CUS / 4) wgrad_go<32, 32, 1>(a, n - tail, tail, up, st);
+            if (tail * m <= cus / 4) wgrad_go<32, 32, 1>(a, n - tail, tail, up, st);
             else wgrad_go<32, 64, 3>(a, n - tail, tail, up, st);
-        } else if (L.cin % 64 == 0 && n * cdiv(L.cout, 32) * (L.cin / 64) >= CUS) {
+        } else if (L.cin % 64 == 0 && n * cdiv(L.cout, 32) * (L.cin / 64) >= cus) {
             wgrad_go<32, 64, 3>(a, 0, n, up, st);
         } else {
             wgrad_go<32, 32, 1>(a, 0, n, up, st);
@@ -313,8 +320,7 @@ radon_status_t radon_cnn_create(radon_cnn_t* out, int batch, int height, int wid
                     height, width);
     radon_cnn_s* c = new (std::nothrow) radon_cnn_s();
     if (!c) return errf(RADON_ERR_OOM, "host allocation failed");
-    if (hipGetDevice(&c->device) != hipSuccess) {
-        (void)hipGetLastError();
+    if (!c->find_device()) {
         delete c;
         return errf(RADON_ERR_DEVICE, "no HIP device");
     }
@@ -474,6 +480,7 @@ radon_status_t radon_cnn_conv_test(const uint16_t* in, const float* w, const flo
     if (!in || !w || B < 1 || Cin < 1 || Cout < 1 || H < 1 || W < 1) return errf(RADON_ERR_INVALID, "bad arguments");
     hipStream_t st = (hipStream_t)stream;
     radon_cnn_s c;
+    if (!c.find_device()) return errf(RADON_ERR_DEVICE, "no HIP device");
     c.B = B;
     Conv L;
     L.cin = Cin;
