@@ -228,7 +228,8 @@ const char* radon_last_error(void);
  * bracketed by HIP events on the caller's stream; radon_plan_stage_times
  * synchronises on those events and returns, per stage, the accumulated
  * milliseconds and launch counts since profiling was switched on. Stage names
- * come from radon_stage_name(0 .. radon_stage_count()-1).
+ * come from radon_stage_name(0 .. radon_stage_count()-1). A2_reduce is retired and
+ * stays at zero: the sums of split strips are part of A3_col_ifft.
  */
 radon_status_t radon_plan_set_profiling(radon_plan_t plan, int enable);
 radon_status_t radon_plan_stage_times(radon_plan_t plan, double* ms, int64_t* counts, int cap);
@@ -303,7 +304,8 @@ typedef struct {
     double x_l1;       /* ||x||_1 of the result                                            */
     double seconds;    /* host wall time of the call                                       */
     int iterations;    /* projected-gradient iterations                                    */
-    int n_forward;     /* radon_forward applications                                       */
+    int n_forward;     /* forward applications whose residual was looked at (a group of
+                          backtracking steps also runs those after the accepted one)       */
     int n_adjoint;     /* radon_adjoint applications                                       */
     int status;        /* 0 iteration limit, 1 basis-pursuit solution, 2 root found        */
     int fallback;      /* why a warm start was abandoned for a cold solve (RADON_FALLBACK_*) */
@@ -330,7 +332,10 @@ enum {
  * with the solution. Vectors are float32; all reductions are float64 in a
  * fixed order, so results are bitwise reproducible. The call allocates its
  * workspace, runs on `stream` and synchronises it (it reads a few float64
- * scalars per iteration); stats may be NULL.
+ * scalars per iteration); stats may be NULL. Backtracking takes four steps at a time
+ * where the plan's workspace for several slices (radon_forward_batched) holds as
+ * many: the first solve that backtracks past two steps allocates it, at most 128
+ * MiB, which stay with the plan until it is destroyed.
  * Warm starts: the cold-started solver is the fallback. A warm run is
  * abandoned for a cold one (stats->fallback says why) when x0 or its first
  * residual is not finite, when x0 fits the data no better than zero, when it

@@ -299,8 +299,8 @@ __device__ __forceinline__ void epilogue(const Epilogue& e, const EpiIn<EPI>& in
 // latency: three waves per SIMD (at most 168 VGPRs) took the layer of 64 -> 32
 // channels at 512 x 512 from 199 to 158 us at batch 8.
 // Measured (256 -> 128 channels on upsampled 128 x 128, batch 8, 77 GFLOP): 108
-// us, 0.72 PFLOP/s of the about 1.25 that this instruction reaches; 350 us for
-// the convolution and 61 us for the upsampling when every operand was four
+// us, 0.72 PFLOP/s of the 1.05 that this instruction reaches on random values
+// (1.24 on zeros); 350 us for the convolution and 61 us for the upsampling when every operand was four
 // 2-byte LDS reads and the loads were not overlapped; 125 us with every piece
 // read by both halves.
 // Grid: x = image tiles, y = channel blocks of CB.

@@ -26,7 +26,7 @@ enum Stage {
     ST_F4,
     ST_A1,
     ST_A2,
-    ST_A2R,
+    ST_A2R,   // retired: the sums of split strips are part of A3; keeps its index and name
     ST_A3,
     ST_A4,
     ST_COUNT
@@ -80,7 +80,7 @@ struct Plan {
     std::vector<F3Item> fitems_h;
     size_t bytes = 0;
     std::vector<void*> allocs;
-    int n_allocs = 0;        // device allocations made while building the plan
+    int n_allocs = 0;        // device allocations asked for so far
     int fail_alloc_at = 0;   // failure-injection hook (RADON_TEST_FAIL_ALLOC), 0: off
 
     bool profiling = false;

@@ -939,9 +939,9 @@ struct SplitSums {
 // Grid line mx (of G = 2 NL points) from the partial sums of the split strips it
 // crosses, added in slot order, for the workgroup that reads the line next: two
 // consecutive my per lane, A2R_FLIGHT slots in flight. A pass of its own costs a
-// launch and the grid's round trip (forward and adjoint of 128 rows, 180 views 38.9 us
-// with it, 37.3 without; 512 and 90 47.0 and 45.3; 1024 and 360 72.6 and 70.0;
-// 2560 and 1024 220.6 and 219.3).
+// launch and the grid's round trip (adjoint of 128 rows, 180 views 22.9 us with it,
+// 21.1 without; 512 and 90 26.0 and 24.2; 1024 and 360 40.8 and 38.8; 1536 and 361
+// 51.9 and 49.6; 2560 and 1024 the same within the spread, 108.3 and 107.9).
 constexpr int A2R_FLIGHT = 8;
 template <int NL, int NT>
 __device__ __forceinline__ void split_sums(int mx, const SplitSums& sp, const float2* __restrict__ partials, float2* grid) {

@@ -306,7 +306,8 @@ class Plan:
         """min ||x||_1 s.t. ||F(A x - sino)||_2 <= sigma (SPGL1). x0: optional
         warm-start image; the library falls back to a cold solve when the warm
         run misbehaves (stats["fallback"] says why, 0 if it did not).
-        Returns (x, stats dict)."""
+        Returns (x, stats dict). The first solve that backtracks may add the plan's
+        workspace for several slices (at most 128 MiB), which stays with the plan."""
         torch = _torch()
         if x0 is None:
             x = torch.zeros((self.n, self.n), dtype=torch.float32, device=sino.device)
@@ -406,7 +407,9 @@ def autotune(n: int, angles, n_det: int, sigma: float = 2.0, W: int = 6, repeats
 class Batch:
     """Uneven slices (distinct plans of any sizes) run together: each
     direction is recorded once per set of buffers into one HIP graph whose
-    branches run slices side by side, then replayed with a single launch."""
+    branches run slices side by side, then replayed with a single launch.
+    n_branches (1..16) is the most branches: batches of few, small slices take
+    one or two, which are faster there. Results do not depend on it."""
 
     def __init__(self, plans, n_branches: int = 4):
         self.plans = list(plans)
