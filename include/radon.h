@@ -359,7 +359,7 @@ radon_status_t radon_solve_bpdn(radon_plan_t plan, const float* b_dev, float* x_
  * the solver's projected-gradient steps (SPGL1, introduction):
  * out = sign(v) max(|v| - lam, 0) with lam >= 0 the exact root of
  * sum max(|v_i| - lam, 0) = tau (lam = 0 when sum |v_i| <= tau; lam at or
- * above max |v_i| when tau = 0), located by a deterministic three-level
+ * above max |v_i|, by at most 1/16 of a normal value, when tau = 0), located by a deterministic three-level
  * radix select on the bit patterns of |v_i|, so the result does not depend
  * on the launch order and lam is exact up to the final float64 sums.
  * v_dev, out_dev: n float32 values on the device (may alias), 16-byte

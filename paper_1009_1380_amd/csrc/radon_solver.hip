@@ -349,8 +349,8 @@ __global__ __launch_bounds__(SV_NT) void k_sv_bb(const float* __restrict__ x, co
 // the next level or, when the root lies in an empty gap, below every element
 // in play, or the bins are single values, gives
 // lam = (sum of |v| above the root - tau) / (their count). Special cases:
-// sum |v| <= tau gives lam = 0 (v is in the ball); tau = 0 gives a lam at or
-// above max |v|; a NaN or infinite v gives lam = NaN, which the soft threshold
+// sum |v| <= tau gives lam = 0 (v is in the ball); tau = 0 gives a lam just
+// above max |v| (PJ_TOP); a NaN or infinite v gives lam = NaN, which the soft threshold
 // turns into NaN outputs.
 // Launches: the level-1, level-2 and level-3 histogram passes, then the soft
 // threshold. There is no grid-wide wait inside a launch: every block of the
@@ -372,6 +372,10 @@ inline int pj_blocks(size_t n) {
 constexpr int PJ_B1 = 11, PJ_B2 = 10, PJ_B3 = 31 - PJ_B1 - PJ_B2;   // bits of the three levels
 constexpr int PJ_BINS = 1 << (PJ_B1 > PJ_B2 ? PJ_B1 : PJ_B2);       // histogram capacity of levels 1 and 2
 constexpr int PJ_BINS3 = 1 << PJ_B3;     // bins of level 3 (one float value each)
+// tau = 0: lam is the upper edge of the values that share max |v|'s leading bits (8
+// of the exponent, 4 of the significand), at most 1/16 above a normal value
+constexpr int PJ_TOP = 12;
+static_assert(PJ_TOP >= PJ_B1 && PJ_TOP <= PJ_B1 + PJ_B2, "the level-2 decision knows these bits");
 
 // Decision after a level: the threshold (done), or the bin to refine (the
 // leading bits of u fixed so far) with the sum and count of |v| above it.
@@ -517,11 +521,12 @@ __device__ PjState pj_decide(const unsigned* __restrict__ hcnt, const unsigned l
             // the root lies below every element in play: all of them are active
             // (aC, aV of thread 0 hold everything)
             d.lam = aC > 0.0 ? fmax(0.0, (aV - tau) / aC) : 0.0;
-        } else if (dS >= tau || L == 3) {
+        } else if ((dS >= tau && (L > 1 || dC > 0.0)) || L == 3) {
             // the root lies above the chosen bin's elements: the active set is
             // everything above the bin (nothing above: tau = 0, all go to zero)
-            d.lam = dC > 0.0 ? (dV - tau) / dC : (double)__uint_as_float(Lv::edge(prefix, (unsigned)bstar + 1u));
-        } else {   // the root is inside bin bstar: the next level refines it
+            const unsigned top = Lv::edge(prefix, (unsigned)bstar) >> (31 - PJ_TOP);
+            d.lam = dC > 0.0 ? (dV - tau) / dC : (double)__uint_as_float((top + 1u) << (31 - PJ_TOP));
+        } else {   // the root is inside bin bstar, or tau = 0: the next level refines it
             d.done = 0.0;
             d.A = dV;
             d.C = dC;
